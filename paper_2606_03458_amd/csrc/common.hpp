@@ -57,11 +57,8 @@ hipError_t launch_append(const kvarn_cache& c, int n_sink, const void* k_new, co
 
 struct DecodePlan {
     int n_chunk, g_chunk;  // query heads of a group taken in n_chunk chunks of up to g_chunk (<= 8)
-    int n_split;           // splits per (sequence, kv head)
-    int n_res;             // splits (the last of n_split) that hold only sink + residual chunks
-    int group;             // > 1: the n_split splits of a stream are the waves of one workgroup
-    int blocks_per_split;  // body tiles per body split
-    int max_blocks_used;   // upper bound of body tiles over the batch
+    int n_wg, group;       // workgroups per (sequence, kv head, chunk) and waves per workgroup
+    int ws_parts;          // partials per query head that the workspace has room for (n_wg <= ws_parts or n_wg == 1)
 };
 
 DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_len, int n_sink, int max_blocks);

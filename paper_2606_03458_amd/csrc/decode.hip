@@ -20,13 +20,18 @@
 // groups are taken in chunks of at most eight heads, one wave per chunk.
 //
 // Sink and residual tokens (bf16, unrotated) use the bf16 matrix cores for q . k (q as a bf16
-// pair hi + lo when it is fp32) and plain FMAs for p . v, in chunks of 32 tokens.  One wave owns
-// a (split, sequence, kv head, head chunk).  An unsplit stream's one wave takes sink + residual
-// after its body tiles; a split stream's sink and residual chunks get splits of their own (one
-// per chunk when the waves fit), which run beside the body splits, or the body splits share
-// them.  A single split writes the final output directly (inverse rotation in LDS); up to four
-// splits of a stream are the waves of one workgroup and combine by log-sum-exp through LDS
-// before writing it; more write partials that the merge kernel combines.
+// pair hi + lo when it is fp32) and plain FMAs for p . v, in chunks of 32 tokens.  The waves of
+// one workgroup share a (sequence, kv head, head chunk): its body tiles and its sink and residual
+// chunks are dealt out as evenly as they go, by the sequence's own length, and the waves' parts
+// are combined by log-sum-exp through LDS, each wave finishing some of the heads.  A workgroup
+// has as many waves as leave every CU full (plan_decode): with one wave per SIMD a wave's chain
+// of loads, LDS exchanges and products is exposed (one tile takes 1.45 us alone, 0.25 us per CU with
+// twelve waves), and a few waves over a long sequence of a ragged batch last longer than the rest
+// of the card.  Against at most four waves, fixed spans of tiles and one wave finishing alone: one
+// layer of 32 sequences at 32k tokens, compact aux, 131 -> 103 us; 48 sequences of 1k to 16k
+// tokens 84 -> 58 us; a step of 64 sequences at 1k tokens 19.6 -> 15.8 us.  Streams with too few
+// workgroups to fill the card take several, whose partials the merge kernel combines (a step of
+// one sequence at 8k tokens 13.8 -> 11.4 us: 17 partials per head instead of 37).
 //
 // A lock-step decode step can append its token in the same launch (Fig. 4): the new row is the
 // residual's last, read from the token input by the wave that attends that chunk, which also
@@ -46,12 +51,9 @@ typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kPart = 260;  // floats per partial: m, l, 2 pad, o_rot[128], o_plain[128]
 constexpr int kRC = 32;     // bf16 tokens (sink / residual) per chunk
-// splits of a stream that may form one workgroup (one wave per SIMD; groups of 5-6 waves
-// measured slower than the separate merge on the 2-bit streaming runs)
-constexpr int kMaxGroup = 4;
-// body tiles below which a stream planned with at most kMaxGroup splits keeps one for its sink
-// and residual chunks
-constexpr int kShortBody = 48;
+// Waves of one workgroup at most: one workgroup then fills a CU (three waves per SIMD for the
+// 2-bit kernels of up to four heads, two for the others).
+constexpr int kMaxGroup3 = 12, kMaxGroup2 = 8;
 
 // A fixed-point grid is only formed for a maximum above this; below it the values are taken
 // as zero.  For p~ this drops a tile whose probabilities are all below 1e-30 relative to the
@@ -78,12 +80,11 @@ struct DecodeArgs {
     int n_phys;                  // pool size in blocks (paged)
     uint32_t* err_word;
     float scale_log2;  // sm_scale * log2(e): logits are kept in log2 units
-    int n_split, bps;  // splits per stream and body tiles per body split
-    int n_res;         // splits that hold only sink + residual chunks (the last n_res of n_split)
     int n_streams;     // batch * n_kv
-    int n_chunk, g_chunk;  // head chunks per stream and heads per chunk (row-digit kernels)
-    int group;         // > 1: the n_split splits of a stream are the waves of one workgroup
-    float* ws;         // [batch][n_q][n_split][kPart] when n_split > 1
+    int n_chunk, g_chunk;  // head chunks per stream and heads per chunk
+    int n_wg, group;   // workgroups per (stream, head chunk), waves per workgroup
+    float inv_waves;   // 1 / (n_wg * group)
+    float* ws;         // [batch][n_q][n_wg][kPart] when n_wg > 1
     // Fused append of a lock-step step: > 0 the common length of the sequences with the token of
     // k_new / v_new ([batch][n_kv][kD] bf16) appended as their last residual row; 0: lengths
     // from seq_len and no append.
@@ -224,52 +225,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// LDS butterflies (stride 1..64) over rows [0, g) of x; one wave.  Unnormalized.
-template <int GQ>
-__device__ __forceinline__ void lds_hadamard(float (&x)[GQ][kD], int g) {
-    const int l = threadIdx.x & 63;
-    for (int h = 1; h < kD; h <<= 1) {
-        for (int idx = l; idx < g * 64; idx += 64) {
-            const int j = idx >> 6, r = idx & 63;
-            const int i0 = (r / h) * 2 * h + (r % h);
-            const float x0 = x[j][i0], x1 = x[j][i0 + h];
-            x[j][i0] = x0 + x1;
-            x[j][i0 + h] = x0 - x1;
-        }
-        wave_sync();
-    }
-}
-
-// Query rows qrow .. qrow + g - 1 into LDS rows 0 .. NR - 1 (rows >= g zero): lane l writes
-// channels 2l, 2l + 1 of every row.  One branch on the dtype, so every load is in flight before
-// the first is used (q is only 4-byte aligned).
-template <int NR>
-__device__ __forceinline__ void q_to_lds(float (&q)[NR][kD], const DecodeArgs& a, size_t qrow, int g, int l) {
-    float v0[NR], v1[NR];
-    if (a.q_bf16) {
-        const uint32_t* q2 = static_cast<const uint32_t*>(a.q);
-#pragma unroll
-        for (int h = 0; h < NR; ++h) {
-            const uint32_t w = q2[(qrow + min(h, g - 1)) * (kD / 2) + l];
-            v0[h] = __uint_as_float(w << 16);
-            v1[h] = __uint_as_float(w & 0xFFFF0000u);
-        }
-    } else {
-        const float* q1 = static_cast<const float*>(a.q);
-#pragma unroll
-        for (int h = 0; h < NR; ++h) {
-            const size_t i = (qrow + min(h, g - 1)) * kD + 2 * l;
-            v0[h] = q1[i];
-            v1[h] = q1[i + 1];
-        }
-    }
-#pragma unroll
-    for (int h = 0; h < NR; ++h) {
-        q[h][2 * l] = h < g ? v0[h] : 0.f;
-        q[h][2 * l + 1] = h < g ? v1[h] : 0.f;
-    }
-}
-
 // NB runs of 8 consecutive query values, run r starting at element idx[r] (a multiple of 8), with
 // one branch on the dtype.
 template <int NB>
@@ -314,6 +269,77 @@ __device__ __forceinline__ float fdpp_x1(float v) { return __int_as_float(dpp_x1
 __device__ __forceinline__ float fdpp_x2(float v) { return __int_as_float(dpp_x2(__float_as_int(v))); }
 __device__ __forceinline__ float fdpp_half_mirror(float v) { return __int_as_float(dpp_half_mirror(__float_as_int(v))); }
 __device__ __forceinline__ float fdpp_mirror(float v) { return __int_as_float(dpp_mirror(__float_as_int(v))); }
+// The 128-point butterflies (unnormalized) over a wave's lanes, lane l holding channels 2l, 2l + 1:
+// stride 1 in the lane, then lane partners l ^ 1, 2, 4, ..., 32, all by lane moves (partner ^4 is
+// the half-row mirror of the quad-reversed value, ^8 a rotation of the row by 8).
+template <int M>
+__device__ __forceinline__ float lane_xor(float v, int l) {
+    if constexpr (M == 1) return fdpp_x1(v);
+    else if constexpr (M == 2) return fdpp_x2(v);
+    else if constexpr (M == 4) return fdpp_half_mirror(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x1B, 0xF, 0xF, true)));
+    else if constexpr (M == 8) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true));
+    else if constexpr (M == 16) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        return __uint_as_float(((l >> 4) & 1) ? x[0] : x[1]);
+    } else {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        return __uint_as_float(l < 32 ? x[1] : x[0]);
+    }
+}
+template <int M>
+__device__ __forceinline__ void fwht_stage(float (&x)[2], int l) {
+    const bool upper = (l & M) != 0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const float p = lane_xor<M>(x[e], l);
+        x[e] = upper ? p - x[e] : x[e] + p;
+    }
+}
+__device__ __forceinline__ void fwht128(float (&x)[2], int l) {
+    const float t = x[0];
+    x[0] = t + x[1];
+    x[1] = t - x[1];
+    fwht_stage<1>(x, l);
+    fwht_stage<2>(x, l);
+    fwht_stage<4>(x, l);
+    fwht_stage<8>(x, l);
+    fwht_stage<16>(x, l);
+    fwht_stage<32>(x, l);
+}
+
+// Query rows qrow .. qrow + g - 1 (lane l holds channels 2l, 2l + 1), rotated and normalized or as
+// given, into LDS rows 0 .. NR - 1 (rows >= g zero).  One branch on the dtype, so every load is in
+// flight before the first is used (q is only 4-byte aligned).  The rotation runs in registers: its
+// seven stages through LDS cost a wave's set-up seven LDS round trips.
+template <int NR>
+__device__ __forceinline__ void q_to_lds(float (&q)[NR][kD], const DecodeArgs& a, size_t qrow, int g, int l) {
+    float v0[NR], v1[NR];
+    if (a.q_bf16) {
+        const uint32_t* q2 = static_cast<const uint32_t*>(a.q);
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+            const uint32_t w = q2[(qrow + min(h, g - 1)) * (kD / 2) + l];
+            v0[h] = __uint_as_float(w << 16);
+            v1[h] = __uint_as_float(w & 0xFFFF0000u);
+        }
+    } else {
+        const float* q1 = static_cast<const float*>(a.q);
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+            const size_t i = (qrow + min(h, g - 1)) * kD + 2 * l;
+            v0[h] = q1[i];
+            v1[h] = q1[i + 1];
+        }
+    }
+    const float qs = a.rotate ? kInvSqrt128 : 1.f;
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+        float x[2] = {v0[h], v1[h]};
+        if (a.rotate) fwht128(x, l);
+        *reinterpret_cast<float2*>(&q[h][2 * l]) = h < g ? make_float2(x[0] * qs, x[1] * qs) : make_float2(0.f, 0.f);
+    }
+}
+
 // max / sum over the 16 lanes of a row (lanes 16G .. 16G + 15): the quad (partners ^1, ^2), then
 // the other quad of the half (mirror within 8), then the other half (mirror within 16).  Every
 // step combines two equal-shaped partial results, so all 16 lanes end with identical values.
@@ -439,10 +465,11 @@ __device__ __forceinline__ uint32_t rows_digit_reduce_scatter4(uint32_t x0, uint
 // channels 16 (4 q + G) + n (sg, q = 0, 1): two values per lane, no padded head slots and no
 // MFMA of its own.
 template <int BITS, int NH, int CMP, int PG, int X1>
-__global__ __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(BITS == 2 && NH == 1 && !X1 ? 3 : 2, 8)))
+__global__ __launch_bounds__(64 * (BITS == 2 && NH == 1 && !X1 ? kMaxGroup3 : kMaxGroup2))
+__attribute__((amdgpu_waves_per_eu(BITS == 2 && NH == 1 && !X1 ? 3 : 2, 8)))
 void k_decode4(DecodeArgs a) {
     static_assert(X1 == 0 || NH == 1, "the extra head is only for one head group");
-    // one LDS block per wave (dynamic: one to kMaxGroup waves per workgroup)
+    // one LDS block per wave (dynamic: a.group waves per workgroup)
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Smem4<NH, X1>& sm = reinterpret_cast<Smem4<NH, X1>*>(dyn_lds)[wave];
@@ -459,31 +486,45 @@ void k_decode4(DecodeArgs a) {
     constexpr uint32_t MAGIC_BITS = 0x4B400000u;
     // output role: head 4*hg + G, column n; A-operand role: row 4*h + j (digit j of head 4*hg + h)
     const int l = threadIdx.x & 63, G = l >> 4, n = l & 15, h = (l >> 2) & 3, j = l & 3;
-    // wave = (head chunk, stream, split), the chunk slowest: the chunks of a stream read the
-    // same tiles, n_streams * n_split waves apart, which keeps them on one XCD when that
-    // distance in workgroups is a multiple of 8.  In group mode a workgroup's waves are the
-    // stream's splits.
-    const int split = a.group > 1 ? wave : blockIdx.x % a.n_split;
-    const int cs = a.group > 1 ? blockIdx.x : blockIdx.x / a.n_split;
-    const int stream = cs % a.n_streams, chunk = cs / a.n_streams;
+    // workgroup = (head chunk, stream, part of the stream), the chunk slowest: the chunks of a
+    // stream read the same tiles, n_streams * n_wg workgroups apart, which keeps them on one XCD
+    // when that distance is a multiple of 8.
+    const int wgi = a.n_wg > 1 ? blockIdx.x % a.n_wg : 0;
+    const int cs = a.n_wg > 1 ? blockIdx.x / a.n_wg : blockIdx.x;
+    const int chunk = a.n_chunk > 1 ? cs / a.n_streams : 0;
+    const int stream = cs - chunk * a.n_streams;
     const int g = min(a.g_chunk, a.g - chunk * a.g_chunk);  // query heads of this wave
     const int b = stream / a.n_kv, kvh = stream % a.n_kv;
-    // A fused append takes the step's length from the host.  The stored length must then be the
-    // one before the append, or the one after it (kv head 0 stores it, perhaps already); else the
-    // sequence is left as it is and bit 2 of err_word is set.
-    const int stored = a.seq_len[b];
-    const bool step_ok = a.step_len == 0 || stored == a.step_len - 1 || stored == a.step_len;
-    const int len = a.step_len > 0 ? a.step_len : max(stored, 0);
+    // A fused append takes the step's length from the host (the stored one is read later, off the
+    // wave's path, and only checked).
+    int len = a.step_len;
+    if (a.step_len == 0) len = max(a.seq_len[b], 0);
     const int ns = min(len, a.n_sink);
     const int nbody = min(len > a.n_sink ? (len - a.n_sink) / kG : 0, a.max_blocks);
     const int nr = len > a.n_sink ? (len - a.n_sink) % kG : 0;
-    // The last n_res splits hold only sink + residual chunks; without them the body splits share
-    // those chunks.
-    const int nbs = a.n_split - a.n_res;  // body splits
-    const bool res_only = split >= nbs;
-    const bool body_last = split == nbs - 1;  // takes any excess of body tiles
-    const int blk0 = res_only ? 0 : split * a.bps;
-    int blk1 = res_only ? 0 : (body_last ? nbody : min(blk0 + a.bps, nbody));
+    // The stream's work in units, its body tiles, then the 32-token chunks of its sink and of its
+    // residual: wave i of the stream's n_waves takes an even share of consecutive units (the first
+    // waves one more where it does not divide), by the sequence's own length, so that the waves
+    // of a short sequence of a ragged batch share its tiles too.
+    const int nsc = (ns + kRC - 1) / kRC, nch = nsc + (nr + kRC - 1) / kRC;
+    const int n_waves = a.n_wg * a.group, wi = wgi * a.group + wave;
+    int blk0 = 0, blk1 = nbody, c0 = 0, c1 = nch;
+    if (n_waves > 1) {
+        const int nu = nbody + nch;
+        int base = (int)((float)nu * a.inv_waves), rem = nu - base * n_waves;  // nu / n_waves, or one off
+        if (rem < 0) {
+            --base;
+            rem += n_waves;
+        } else if (rem >= n_waves) {
+            ++base;
+            rem -= n_waves;
+        }
+        const int u0 = wi * base + min(wi, rem), u1 = u0 + base + (wi < rem ? 1 : 0);
+        blk0 = min(u0, nbody);
+        blk1 = min(u1, nbody);
+        c0 = max(u0 - nbody, 0);
+        c1 = max(u1 - nbody, 0);
+    }
     if (PG && blk0 < blk1 && !body_ids_ok(a, b, blk0, blk1, l)) blk1 = blk0;
     const size_t qrow = (size_t)b * a.n_q + (size_t)kvh * a.g + (size_t)chunk * a.g_chunk;
     const size_t tb = tile_bytes(BITS, CMP), cb = code_bytes(BITS);
@@ -578,22 +619,16 @@ void k_decode4(DecodeArgs a) {
             sm.qp[idx >> 5][3][(idx >> 4) & 1][idx & 15] = make_uint4(0u, 0u, 0u, 0u);
         if (X1 && l < 8) sm.qp4[X1 ? 3 : 0][l >> 2][l & 3] = make_uint4(0u, 0u, 0u, 0u);
         wave_sync();
-        if (a.rotate) lds_hadamard<NHX>(sm.q, g);
-        // q~ role: head 4*hg + G, channels 8n .. 8n + 7 (rotated and normalized, or as given)
-        const float qs = a.rotate ? kInvSqrt128 : 1.f;
-        // two head groups: q stays in LDS (each lane scales, and later reads, only its own
-        // elements), which keeps 16 registers free for the tile loop
+        // q~ role: head 4*hg + G, channels 8n .. 8n + 7.  Two head groups: q stays in LDS, which keeps
+        // 16 registers free for the tile loop.
         constexpr bool QLDS = NH == 2;
-        float qr[QLDS ? 1 : NH][8];
+        float qr[8];
+        if constexpr (!QLDS) {
 #pragma unroll
-        for (int hg = 0; hg < NH; ++hg)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if constexpr (QLDS) sm.q[4 * hg + G][8 * n + k] *= qs;
-                else qr[hg][k] = sm.q[4 * hg + G][8 * n + k] * qs;
-            }
+            for (int k = 0; k < 8; ++k) qr[k] = sm.q[G][8 * n + k];
+        }
         // extra head: channels 2l, 2l + 1
-        const float qr4[2] = {X1 ? sm.q[NHX - 1][2 * l] * qs : 0.f, X1 ? sm.q[NHX - 1][2 * l + 1] * qs : 0.f};
+        const float qr4[2] = {X1 ? sm.q[NHX - 1][2 * l] : 0.f, X1 ? sm.q[NHX - 1][2 * l + 1] : 0.f};
         // source lane of the PV operand permutation (see above), as a byte address; for the
         // extra head the source row is the token block (tau), not the head
         const int perm_addr = (16 * h + 4 * G + j) * 4;
@@ -643,7 +678,7 @@ void k_decode4(DecodeArgs a) {
                         qv[4] = x1.x; qv[5] = x1.y; qv[6] = x1.z; qv[7] = x1.w;
                     } else {
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) qv[k] = qr[QLDS ? 0 : hg][k];
+                        for (int k = 0; k < 8; ++k) qv[k] = qr[k];
                     }
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
@@ -847,17 +882,13 @@ void k_decode4(DecodeArgs a) {
     }
 
     // ---- sink and residual (bf16, unrotated) -------------------------------------------------
-    // In chunks of kRC tokens: the sink's, then the residual's (no chunk spans both).  Split r of
-    // the n_res sink/residual splits takes chunks r, r + n_res, ...; without such splits, split r
-    // of the stream takes chunks r, r + n_split, ....  A chunk's key rows (bf16 MFMA operands)
-    // and value rows (one dword per lane and row) are loaded together, one memory round trip per
-    // chunk.
+    // In chunks of kRC tokens: the sink's, then the residual's (no chunk spans both).  A chunk's key
+    // rows (bf16 MFMA operands) and value rows (one dword per lane and row) are loaded together,
+    // one memory round trip per chunk.
     float oplain[NHX][2];  // head hh, channel 2*l + jj (unrotated)
 #pragma unroll
     for (int hh = 0; hh < NHX; ++hh) oplain[hh][0] = oplain[hh][1] = 0.f;
-    const int nsc = (ns + kRC - 1) / kRC, nch = nsc + (nr + kRC - 1) / kRC;
-    const int c0 = res_only ? split - nbs : split, cstep = res_only ? a.n_res : a.n_split;
-    if ((res_only || a.n_res == 0) && c0 < nch) {
+    if (c0 < c1) {
         // A operand of group hg: row 4h holds q of head 4*hg + h rounded to bf16, row 4h + 1 the
         // remainder (zero for bf16 q), rows 4h + 2, 4h + 3 zero; lane (G, 4h + j) holds
         // q[.][32k + 8G ..].  Loads are clamped to a valid head, then masked.
@@ -902,7 +933,7 @@ void k_decode4(DecodeArgs a) {
                     aqs4[k][e] = j == 0 ? hi : (__bf16)(v - (float)hi);
                 }
         }
-        for (int c = c0; c < nch; c += cstep) {
+        for (int c = c0; c < c1; ++c) {
             const bool in_sink = c < nsc;
             const int t0 = kRC * (in_sink ? c : c - nsc);
             const int cn = min(kRC, (in_sink ? ns : nr) - t0);
@@ -929,15 +960,20 @@ void k_decode4(DecodeArgs a) {
             uint32_t v2[kRC];  // value row t, channels 2 l, 2 l + 1
 #pragma unroll
             for (int t = 0; t < kRC; ++t) v2[t] = reinterpret_cast<const uint32_t*>(t < cn - 1 ? Vp + (size_t)t * kD : Vlast)[l];
-            if (new_row && chunk == 0 && step_ok) {
-                // the token into the residual (one head chunk writes it), and the step's length
-                // (kv head 0 of the sequence writes it)
-                reinterpret_cast<uint32_t*>(a.k_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Klast)[l];
-                reinterpret_cast<uint32_t*>(a.v_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Vlast)[l];
-                if (kvh == 0 && l == 0) __hip_atomic_store(a.seq_len + b, a.step_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (new_row && chunk == 0) {
+                // The token into the residual (one head chunk writes it), and the step's length (kv
+                // head 0 of the sequence writes it).  The stored length must be the one before the
+                // append, or the one after it (kv head 0 may have stored it already); else the
+                // sequence is left as it is and bit 2 of err_word is set.
+                const int stored = __hip_atomic_load(a.seq_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (stored == a.step_len - 1 || stored == a.step_len) {
+                    reinterpret_cast<uint32_t*>(a.k_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Klast)[l];
+                    reinterpret_cast<uint32_t*>(a.v_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Vlast)[l];
+                    if (kvh == 0 && l == 0) __hip_atomic_store(a.seq_len + b, a.step_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else if (l == 0 && a.err_word) {
+                    __hip_atomic_fetch_or(a.err_word, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
-            if (new_row && chunk == 0 && !step_ok && l == 0 && a.err_word)
-                __hip_atomic_fetch_or(a.err_word, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wave_sync();  // the previous chunk is done with sm.p / sm.hv
             // logits of head 4*hg + G, token 16*tau + n
             float lg[NH][2];
@@ -1002,162 +1038,74 @@ void k_decode4(DecodeArgs a) {
     }
 
     // ---- finish ------------------------------------------------------------------------------
-    float lt[NH];
-#pragma unroll
-    for (int hg = 0; hg < NH; ++hg) lt[hg] = row_sum(l_run[hg]);
-    float lt4 = X1 ? wave_sum(l4) : 0.f;
-    if (a.group > 1) {
-        // Log-sum-exp of the splits inside the workgroup: every wave w > 0 leaves its part
-        // (rotated output per head and channel, plain output, m and l per head slot) in its own
-        // LDS block; wave 0 rescales all parts to their common maximum, adds them in wave order
-        // and writes the output as an unsplit stream does.
-        auto part = [&](int w) { return reinterpret_cast<float*>(reinterpret_cast<Smem4<NH, X1>*>(dyn_lds) + w); };
-        // in each block: [NHX][kD] rotated output, [NHX][kD] plain output, [NHX] m, [NHX] l; block
-        // 1 also [NHX] m of wave 0
-        constexpr int XP = NHX * kD, XM = 2 * NHX * kD;
-        static_assert(sizeof(Smem4<NH, X1>) >= sizeof(float) * (2 * NHX * kD + 3 * NHX), "exchange area");
-        if (wave > 0) {
-            float* xb = part(wave);
-#pragma unroll
-            for (int hg = 0; hg < NH; ++hg) {
-#pragma unroll
-                for (int mt = 0; mt < 8; ++mt) xb[(4 * hg + G) * kD + 16 * mt + n] = orot[hg][mt];
-                if (n == 0) {
-                    xb[XM + 4 * hg + G] = m_run[hg];
-                    xb[XM + NHX + 4 * hg + G] = lt[hg];
-                }
-            }
-            if constexpr (X1) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) xb[(NHX - 1) * kD + 16 * (4 * q + G) + n] = orot4[q];
-                if (l == 0) {
-                    xb[XM + NHX - 1] = m4;
-                    xb[XM + 2 * NHX - 1] = lt4;
-                }
-            }
-#pragma unroll
-            for (int hh = 0; hh < NHX; ++hh)
-                *reinterpret_cast<float2*>(xb + XP + hh * kD + 2 * l) = make_float2(oplain[hh][0], oplain[hh][1]);
-        }
-        __syncthreads();
-        if (wave > 0) return;
-        const int np = a.group;
-        auto ex = [](float m, float M) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M); };
+    // Every wave leaves its part in its own LDS block: [NHX][kD] rotated output, [NHX][kD] plain
+    // output, [NHX] m, [NHX] l.  Then the workgroup's waves take the heads in turn: log-sum-exp of the
+    // waves' parts in wave order (lane l holds channels 2l, 2l + 1), and either the output (inverse
+    // rotation in registers, normalisation) or, where the stream has several workgroups, the
+    // workgroup's partial.
+    auto part = [&](int w) { return reinterpret_cast<float*>(reinterpret_cast<Smem4<NH, X1>*>(dyn_lds) + w); };
+    constexpr int XP = NHX * kD, XM = 2 * NHX * kD, XL = XM + NHX;
+    static_assert(sizeof(Smem4<NH, X1>) >= sizeof(float) * (2 * NHX * kD + 2 * NHX), "exchange area");
+    wave_sync();  // this wave is done with sm
+    {
+        float* xb = part(wave);
 #pragma unroll
         for (int hg = 0; hg < NH; ++hg) {
-            const int hs = 4 * hg + G;
-            float M = m_run[hg];
-            for (int w = 1; w < np; ++w) M = fmaxf(M, part(w)[XM + hs]);
-            const float w0 = ex(m_run[hg], M);
-            lt[hg] *= w0;
+            const float lt = row_sum(l_run[hg]);
 #pragma unroll
-            for (int mt = 0; mt < 8; ++mt) orot[hg][mt] *= w0;
-            for (int w = 1; w < np; ++w) {
-                const float* xb = part(w);
-                const float ww = ex(xb[XM + hs], M);
-                lt[hg] = fmaf(ww, xb[XM + NHX + hs], lt[hg]);
-#pragma unroll
-                for (int mt = 0; mt < 8; ++mt) orot[hg][mt] = fmaf(ww, xb[hs * kD + 16 * mt + n], orot[hg][mt]);
-            }
-            if (n == 0) part(1)[XM + 2 * NHX + hs] = m_run[hg];
-        }
-        if constexpr (X1) {
-            float M = m4;
-            for (int w = 1; w < np; ++w) M = fmaxf(M, part(w)[XM + NHX - 1]);
-            const float w0 = ex(m4, M);
-            lt4 *= w0;
-            orot4[0] *= w0;
-            orot4[1] *= w0;
-            for (int w = 1; w < np; ++w) {
-                const float* xb = part(w);
-                const float ww = ex(xb[XM + NHX - 1], M);
-                lt4 = fmaf(ww, xb[XM + 2 * NHX - 1], lt4);
-#pragma unroll
-                for (int q = 0; q < 2; ++q) orot4[q] = fmaf(ww, xb[(NHX - 1) * kD + 16 * (4 * q + G) + n], orot4[q]);
-            }
-            if (l == 0) part(1)[XM + 3 * NHX - 1] = m4;
-        }
-        wave_sync();
-#pragma unroll
-        for (int hh = 0; hh < NHX; ++hh) {
-            const float m0 = part(1)[XM + 2 * NHX + hh];
-            float M = m0;
-            for (int w = 1; w < np; ++w) M = fmaxf(M, part(w)[XM + hh]);
-            const float w0 = ex(m0, M);
-            oplain[hh][0] *= w0;
-            oplain[hh][1] *= w0;
-            for (int w = 1; w < np; ++w) {
-                const float* xb = part(w);
-                const float ww = ex(xb[XM + hh], M);
-                const float2 y = *reinterpret_cast<const float2*>(xb + XP + hh * kD + 2 * l);
-                oplain[hh][0] = fmaf(ww, y.x, oplain[hh][0]);
-                oplain[hh][1] = fmaf(ww, y.y, oplain[hh][1]);
-            }
-        }
-    }
-    if (a.n_split == 1 || a.group > 1) {
-        wave_sync();
-#pragma unroll
-        for (int hg = 0; hg < NH; ++hg) {
-            if (4 * hg + G < g) {
-#pragma unroll
-                for (int mt = 0; mt < 8; ++mt) sm.q[4 * hg + G][16 * mt + n] = orot[hg][mt];
-                if (n == 0) sm.hv[4 * hg + G][3] = lt[hg];
+            for (int mt = 0; mt < 8; ++mt) xb[(4 * hg + G) * kD + 16 * mt + n] = orot[hg][mt];
+            if (n == 0) {
+                xb[XM + 4 * hg + G] = m_run[hg];
+                xb[XL + 4 * hg + G] = lt;
             }
         }
         if constexpr (X1) {
+            const float lt4 = wave_sum(l4);
 #pragma unroll
-            for (int q = 0; q < 2; ++q) sm.q[NHX - 1][16 * (4 * q + G) + n] = orot4[q];
-            if (l == 0) sm.hv[NHX - 1][3] = lt4;
-        }
-        wave_sync();
-        if (a.rotate) lds_hadamard<NHX>(sm.q, g);
-        const float rs = a.rotate ? kInvSqrt128 : 1.f;
-#pragma unroll
-        for (int hh = 0; hh < NHX; ++hh) {
-            if (hh < g) {
-                const float L = sm.hv[hh][3];
-                float o0 = sm.q[hh][2 * l] * rs + oplain[hh][0];
-                float o1 = sm.q[hh][2 * l + 1] * rs + oplain[hh][1];
-                o0 = L > 0.f ? o0 / L : 0.f;
-                o1 = L > 0.f ? o1 / L : 0.f;
-                const size_t idx = (qrow + hh) * kD + 2 * l;
-                if (a.out_bf16)
-                    reinterpret_cast<uint32_t*>(a.out)[idx >> 1] =
-                        (uint32_t)f32_to_bf16(o0) | ((uint32_t)f32_to_bf16(o1) << 16);
-                else
-                    *reinterpret_cast<float2*>(static_cast<float*>(a.out) + idx) = make_float2(o0, o1);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int hg = 0; hg < NH; ++hg) {
-            if (4 * hg + G < g) {
-                float* P = a.ws + ((qrow + 4 * hg + G) * a.n_split + split) * kPart;
-#pragma unroll
-                for (int mt = 0; mt < 8; ++mt) P[4 + 16 * mt + n] = orot[hg][mt];
-                if (n == 0) {
-                    P[0] = m_run[hg];
-                    P[1] = lt[hg];
-                }
-            }
-        }
-        if (X1 && g == NHX) {  // a chunk of a larger group may leave the extra head slot empty
-            float* P = a.ws + ((qrow + NHX - 1) * a.n_split + split) * kPart;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) P[4 + 16 * (4 * q + G) + n] = orot4[q];
+            for (int q = 0; q < 2; ++q) xb[(NHX - 1) * kD + 16 * (4 * q + G) + n] = orot4[q];
             if (l == 0) {
-                P[0] = m4;
-                P[1] = lt4;
+                xb[XM + NHX - 1] = m4;
+                xb[XL + NHX - 1] = lt4;
             }
         }
 #pragma unroll
-        for (int hh = 0; hh < NHX; ++hh) {
-            if (hh < g) {
-                float* P = a.ws + ((qrow + hh) * a.n_split + split) * kPart;
-                *reinterpret_cast<float2*>(P + 132 + 2 * l) = make_float2(oplain[hh][0], oplain[hh][1]);
-            }
+        for (int hh = 0; hh < NHX; ++hh)
+            *reinterpret_cast<float2*>(xb + XP + hh * kD + 2 * l) = make_float2(oplain[hh][0], oplain[hh][1]);
+    }
+    __syncthreads();
+    const float rs = a.rotate ? kInvSqrt128 : 1.f;
+    for (int hh = wave; hh < g; hh += a.group) {
+        float M = -INFINITY;
+        for (int w = 0; w < a.group; ++w) M = fmaxf(M, part(w)[XM + hh]);
+        float L = 0.f, acc[2] = {0.f, 0.f}, pl[2] = {0.f, 0.f};
+        for (int w = 0; w < a.group; ++w) {
+            const float* xb = part(w);
+            const float m = xb[XM + hh];
+            const float ww = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+            const float2 x = *reinterpret_cast<const float2*>(xb + hh * kD + 2 * l);
+            const float2 y = *reinterpret_cast<const float2*>(xb + XP + hh * kD + 2 * l);
+            L = fmaf(ww, xb[XL + hh], L);
+            acc[0] = fmaf(ww, x.x, acc[0]);
+            acc[1] = fmaf(ww, x.y, acc[1]);
+            pl[0] = fmaf(ww, y.x, pl[0]);
+            pl[1] = fmaf(ww, y.y, pl[1]);
         }
+        if (a.n_wg > 1) {
+            float* P = a.ws + ((qrow + hh) * a.n_wg + wgi) * kPart;
+            if (l == 0) *reinterpret_cast<float2*>(P) = make_float2(M, L);
+            *reinterpret_cast<float2*>(P + 4 + 2 * l) = make_float2(acc[0], acc[1]);
+            *reinterpret_cast<float2*>(P + 132 + 2 * l) = make_float2(pl[0], pl[1]);
+            continue;
+        }
+        if (a.rotate) fwht128(acc, l);
+        float o0 = acc[0] * rs + pl[0], o1 = acc[1] * rs + pl[1];
+        o0 = L > 0.f ? o0 / L : 0.f;
+        o1 = L > 0.f ? o1 / L : 0.f;
+        const size_t idx = (qrow + hh) * kD + 2 * l;
+        if (a.out_bf16)
+            reinterpret_cast<uint32_t*>(a.out)[idx >> 1] = (uint32_t)f32_to_bf16(o0) | ((uint32_t)f32_to_bf16(o1) << 16);
+        else
+            *reinterpret_cast<float2*>(static_cast<float*>(a.out) + idx) = make_float2(o0, o1);
     }
 }
 
@@ -1167,33 +1115,6 @@ void k_decode4(DecodeArgs a) {
 // workgroup) for few splits; W = 4 for many, wave w summing splits w, w + 4, ... and wave 0
 // adding the four sums in a fixed order (eight waves per head measured slower at 37 splits).
 constexpr int kMergeWide = 9;  // from this many splits on, four waves per head
-
-// Channel partner c ^ (2 m) of lane l's two channels: the value of lane l ^ m.
-template <int M>
-__device__ __forceinline__ float lane_xor(float v, int l) {
-    if constexpr (M == 1) return fdpp_x1(v);
-    else if constexpr (M == 2) return fdpp_x2(v);
-    else if constexpr (M == 16) {
-        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        return __uint_as_float(((l >> 4) & 1) ? x[0] : x[1]);
-    } else if constexpr (M == 32) {
-        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        return __uint_as_float(l < 32 ? x[1] : x[0]);
-    } else {
-        return __shfl_xor(v, M);
-    }
-}
-// One butterfly stage of stride 2 M between lanes l and l ^ M (both channels): the lower
-// channel keeps a + b, the upper one a - b.
-template <int M>
-__device__ __forceinline__ void fwht_stage(float (&x)[2], int l) {
-    const bool upper = (l & M) != 0;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const float p = lane_xor<M>(x[e], l);
-        x[e] = upper ? p - x[e] : x[e] + p;
-    }
-}
 
 template <int W>
 __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
@@ -1207,8 +1128,8 @@ __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
     const size_t bh = (size_t)blockIdx.x * HPB + wv / W;
     // W > 1: one head per workgroup, so every wave leaves here or none does.
     if (bh >= (size_t)a.n_streams / a.n_kv * a.n_q) return;
-    const float* P = a.ws + bh * a.n_split * kPart;
-    const int S = a.n_split;
+    const float* P = a.ws + bh * a.n_wg * kPart;
+    const int S = a.n_wg;
     // Log-sum-exp over this wave's splits, U of them with every load in flight (indices past the
     // last split are clamped, their values unused), the sums kept relative to the running
     // maximum M of the splits that hold a probability mass.
@@ -1289,17 +1210,7 @@ __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
             }
         }
     }
-    if (a.rotate) {  // H o_rot: butterflies of stride 1 (in the lane), 2, 4, ..., 64
-        const float t = acc[0];
-        acc[0] = t + acc[1];
-        acc[1] = t - acc[1];
-        fwht_stage<1>(acc, l);
-        fwht_stage<2>(acc, l);
-        fwht_stage<4>(acc, l);
-        fwht_stage<8>(acc, l);
-        fwht_stage<16>(acc, l);
-        fwht_stage<32>(acc, l);
-    }
+    if (a.rotate) fwht128(acc, l);
     const float rs = a.rotate ? kInvSqrt128 : 1.f;
     float o[2];
 #pragma unroll
@@ -1317,9 +1228,8 @@ __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
 template <int BITS, int GQ, int CMP>
 hipError_t launch_cfg(const DecodeArgs& a, int batch, hipStream_t stream) {
     const int streams = batch * a.n_kv;
-    // group mode: one workgroup of n_split waves per (stream, chunk); else one wave per workgroup
-    const int wpg = a.group > 1 ? a.group : 1;
-    const dim3 grid((unsigned)(streams * a.n_chunk * (a.group > 1 ? 1 : a.n_split))), block(64 * wpg);
+    const int wpg = a.group;
+    const dim3 grid((unsigned)(streams * a.n_chunk * a.n_wg)), block(64 * wpg);
     const bool pg = a.block_table != nullptr;
     if constexpr (GQ == 4) {
         const size_t lds = wpg * sizeof(Smem4<1, 0>);
@@ -1335,9 +1245,9 @@ hipError_t launch_cfg(const DecodeArgs& a, int batch, hipStream_t stream) {
         else hipLaunchKernelGGL((k_decode4<BITS, 2, CMP, 0, 0>), grid, block, lds, stream, a);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.n_split == 1 || a.group > 1) return e;
+    if (e != hipSuccess || a.n_wg == 1) return e;
     const size_t heads = (size_t)batch * a.n_q;
-    if (a.n_split >= kMergeWide)
+    if (a.n_wg >= kMergeWide)
         hipLaunchKernelGGL(k_decode_merge<4>, dim3((unsigned)heads), dim3(256), 0, stream, a);
     else
         hipLaunchKernelGGL(k_decode_merge<1>, dim3((unsigned)((heads + 3) / 4)), dim3(256), 0, stream, a);
@@ -1353,73 +1263,71 @@ hipError_t launch_bits(const DecodeArgs& a, int batch, hipStream_t stream) {
 
 }  // namespace
 
+// Partials per query head that kvarn_decode_workspace_bytes leaves room for: one for each share
+// of at least two body tiles and one per sink or residual chunk, of the streams (sequence, kv
+// head, head chunk) that are too few to fill the card; 0 where no plan writes partials.  Callers
+// keep buffers of this size, so it is part of the interface; a plan takes fewer.
+static int workspace_parts(long long streams, int nb, int max_len, int n_sink, int per_simd) {
+    const long long slots = 1024LL * per_simd;
+    if (streams * 4 >= 1024) return 0;
+    const int want = (int)std::min<long long>((slots + streams - 1) / streams, nb / 2);
+    if (want < 2) return 0;
+    const int bps = (nb + want - 1) / want, body = (nb + bps - 1) / bps;
+    const int chunks = (std::min(n_sink, std::max(max_len, 0)) + kRC - 1) / kRC + kG / kRC;
+    const int parts = body + (streams * (body + chunks) <= slots ? chunks : streams * (body + 1) <= slots ? 1 : 0);
+    return parts <= 4 ? 0 : parts;
+}
+
 DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_len, int n_sink, int max_blocks) {
     DecodePlan p;
-    int nb = max_len > n_sink ? (max_len - n_sink) / kG : 0;
-    if (nb > max_blocks) nb = max_blocks;
-    p.max_blocks_used = nb;
+    const int nb = std::min(max_len > n_sink ? (max_len - n_sink) / kG : 0, max_blocks);
     const int g = n_kv > 0 ? n_q / n_kv : 1;
-    // Groups above 8 query heads go to the row-digit kernels in chunks of at most 8 heads (as
-    // even as possible), one wave per chunk; the chunks of a stream read the same tiles.
+    // Groups above 8 query heads go to the kernels in chunks of at most 8 heads (as even as
+    // possible); the chunks of a stream read the same tiles.
     p.n_chunk = (g + 7) / 8;
     p.g_chunk = (g + p.n_chunk - 1) / p.n_chunk;
-    const int gc = p.g_chunk;
-    const int streams = batch * n_kv * p.n_chunk;  // waves per split
-    // one wave per (split, chunk, stream).  Aim for one round of resident waves (the kernels'
-    // occupancy on 1024 SIMDs), with at least 2 body tiles per split so that the per-wave
-    // setup and the merge stay small against the streaming (measured on the Llama layer,
-    // decode + merge: 1 tile per split 15.6 us, 2 tiles 14.1 us, 4 tiles 17.8 us).
-    const int per_simd = gc <= 4 ? (bits == 2 ? 3 : 2) : 2;
-    int want = (1024 * per_simd + streams - 1) / streams;
-    // When kMaxGroup splits per stream already give every SIMD a wave, stop there: the splits
-    // then merge inside their workgroup (no partials, no merge launch) and fewer, longer splits
-    // spend less on per-split set-up, which beats filling the round (measured on 2-bit tiles,
-    // 512 streams: 231 us instead of 242 at 32k tokens, 18-21 us instead of 23 at 1k; 256
-    // streams: 123 us instead of 138 at 32k).
-    const bool few = (long long)streams * kMaxGroup >= 1024;
-    if (few && want > kMaxGroup) want = kMaxGroup;
-    // Short streams there give one of those waves to the sink and residual chunks, which then run
-    // beside the body tiles instead of after them, if the extra wave still fits the round (512
-    // streams at 1k tokens: 17.9 us instead of 20.1, at 4k 39.4 instead of 41.3; from 8k on the
-    // body splits gain more than that).
-    const bool res_split = few && nb < kShortBody &&
-                           (long long)streams * (std::min(want, kMaxGroup - 1) + 1) <= 1024LL * per_simd;
-    if (res_split && want > kMaxGroup - 1) want = kMaxGroup - 1;
-    if (want > nb / 2) want = nb / 2;
-    p.n_res = 0;
-    p.group = 0;
-    if (want < 1 || (want == 1 && !res_split)) {
-        p.n_split = 1;
-        p.blocks_per_split = nb > 0 ? nb : 1;
-        return p;
+    const long long streams = (long long)batch * n_kv * p.n_chunk;
+    const int per_simd = bits == 2 && p.g_chunk <= 4 ? 3 : 2, per_cu = 4 * per_simd;
+    p.ws_parts = workspace_parts(streams, nb, max_len, n_sink, per_simd);
+    const int units = nb + (std::min(n_sink, std::max(max_len, 0)) + kRC - 1) / kRC + kG / kRC;
+    // Waves per workgroup: a CU holds per_cu waves, and a workgroup merges its waves' parts in LDS.
+    // The lines below were measured with 8 kv heads, every plan in turn (us at 2 bits, group size 4
+    // unless said otherwise).
+    p.n_wg = 1;
+    if (streams > 768) {
+        // enough streams to fill the card with one or two waves each (16k tokens: 1024 streams 231 /
+        // 226 / 229 with 1 / 2 / 4 waves, 2048 streams 446 / 490 / 453)
+        p.group = 2 * streams <= 1024LL * per_simd ? 2 : 1;
+    } else if (streams > 256) {
+        // Four waves, one per SIMD, so that two workgroups share a CU (512 streams, 1.1k tokens: 23 / 21
+        // / 28 / 30 with 3 / 4 / 6 / 12 waves; groups that are not a multiple of four load the SIMDs
+        // unevenly).  Long sequences take a whole CU in turn: level or up to 4 % slower where all are
+        // equally long, a fifth faster where lengths differ (384 streams of 1k to 16k tokens: 73 with
+        // 4 waves, 58 with 12), since a sequence then takes as long as its own tiles.
+        p.group = nb >= 96 ? per_cu : 4;
+    } else {
+        // A CU or more per stream.  Few units: eight waves of one or two units each (8 streams, 1k
+        // tokens: 9.5 / 7.9 / 8.8 with 4 / 8 / 12 waves); more: all the CU's waves (2k tokens: 12.4 /
+        // 10.2 / 10.0).
+        p.group = units <= 16 ? std::min(8, units) : per_cu;
+        // Several workgroups per stream cost a merge launch (about 4 us) and pay once they take some
+        // 20 units off each workgroup (8 streams, 2k tokens: 10.0 alone, 10.0 to 11 shared; 4k: 15.1 alone,
+        // 11.0 shared; 128 streams, 4k: 16.5 and 16.8, 16k: 43 and 39).
+        const int per_wg = p.g_chunk > 5 ? 2 : 4;
+        const int n = std::min({(int)(256 / std::max(streams, 1LL)), (units + per_wg - 1) / per_wg, p.ws_parts});
+        if (n > 1 && (long long)units * (n - 1) > 20LL * n) {
+            // one wave per SIMD unless more shorten the longest wave's run of tiles (32 streams, 16k
+            // tokens: 18.0 / 16.8 / 18.8 with 4 / 6 / 12 waves in 8 workgroups)
+            const int more = per_simd == 3 ? 6 : 8;
+            p.n_wg = n;
+            p.group = (nb + n * more - 1) / (n * more) < (nb + n * 4 - 1) / (n * 4) ? more : 4;
+        }
     }
-    p.blocks_per_split = (nb + want - 1) / want;
-    p.n_split = (nb + p.blocks_per_split - 1) / p.blocks_per_split;
-    // A split stream is merged anyway: its sink + residual chunks (bf16, one memory round trip
-    // each) get splits of their own, one per chunk a stream can hold, which run beside the body
-    // splits -- when the extra waves still fit in the one round of resident waves (otherwise
-    // body waves would wait for free slots behind them; measured: GQA-5 stress 28 % slower);
-    // else one such split for all chunks if that fits.
-    // (With kMaxGroup splits or fewer per stream the body splits share the chunks instead, unless
-    // a short stream keeps a split for them, above.)
-    const int chunks = (std::min(n_sink, std::max(max_len, 0)) + kRC - 1) / kRC + kG / kRC;
-    if (few)
-        p.n_res = res_split ? 1 : 0;
-    else if ((long long)streams * (p.n_split + chunks) <= 1024LL * per_simd)
-        p.n_res = chunks;
-    else if ((long long)streams * (p.n_split + 1) <= 1024LL * per_simd)
-        p.n_res = 1;
-    p.n_split += p.n_res;
-    // Up to kMaxGroup splits: the waves of one workgroup, merged there (no partials in memory,
-    // no merge launch), when their LDS blocks fit the workgroup's 64 KB.
-    const size_t blk = gc <= 4 ? sizeof(Smem4<1, 0>) : gc == 5 ? sizeof(Smem4<1, 1>) : sizeof(Smem4<2, 0>);
-    if (p.n_split <= kMaxGroup && p.n_split * blk <= 65536) p.group = p.n_split;
     return p;
 }
 
 size_t decode_workspace_bytes(int batch, int n_q, const DecodePlan& plan) {
-    if (plan.n_split == 1 || plan.group > 1) return 0;
-    return (size_t)batch * n_q * plan.n_split * kPart * sizeof(float);
+    return (size_t)batch * n_q * plan.ws_parts * kPart * sizeof(float);
 }
 
 hipError_t launch_decode(const kvarn_cache& c, int bits, int compact, int rotate, int n_sink, int n_q, const void* q,
@@ -1447,10 +1355,9 @@ hipError_t launch_decode(const kvarn_cache& c, int bits, int compact, int rotate
     a.max_blocks = c.max_blocks;
     a.n_sink = n_sink;
     a.scale_log2 = sm_scale * kLog2e;
-    a.n_split = plan.n_split;
-    a.bps = plan.blocks_per_split;
-    a.n_res = plan.n_res;
+    a.n_wg = plan.n_wg;
     a.group = plan.group;
+    a.inv_waves = 1.f / (float)(plan.n_wg * plan.group);
     a.n_streams = c.batch * c.n_kv;
     a.n_chunk = plan.n_chunk;
     a.g_chunk = plan.g_chunk;
