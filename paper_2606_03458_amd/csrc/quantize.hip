@@ -808,6 +808,7 @@ struct PrefillArgs {
     const int32_t* cu;  // [batch + 1] prompt offsets (rows of k, v)
     int max_len;
     int groups;         // body tiles per (sequence, kv head) the grid covers
+    int64_t tile_blocks;  // workgroups of tiles; the rest copy bf16 rows
 };
 
 // Prompt length of sequence b, or -1 when it cannot be written (longer than the launch bound or
@@ -818,11 +819,71 @@ __device__ __forceinline__ int prefill_len(const PrefillArgs& a, int b) {
     return (L < 0 || L > a.max_len || nb > a.c.max_blocks) ? -1 : L;
 }
 
-// One workgroup per (sequence, kv head, K|V, body tile): quantizes the prompt's tile straight
-// from the packed rows (token stride n_kv * 128 elements).
+// Sink and residual rows of one (sequence, kv head, K|V) as bf16, and the sequence's length.  Bound by
+// latency: 8 channels per lane and four rows in flight (2-byte accesses in a launch of their own took
+// 48 us for 12 prompts of up to 4k tokens, 8 kv heads, with a 128-token sink; beside the tiles, 0).
+__device__ __forceinline__ void prefill_copy(const PrefillArgs& a, int64_t stream, int kind) {
+    const int b = (int)(stream / a.c.n_kv), kh = (int)(stream % a.c.n_kv);
+    const int L = prefill_len(a, b);
+    if (threadIdx.x == 0 && kh == 0 && kind == 0) {
+        a.c.seq_len[b] = L < 0 ? 0 : L;
+        if (L < 0 && a.c.err_word)
+            __hip_atomic_fetch_or(a.c.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (L < 0) return;
+    const int ns = min(L, a.n_sink);
+    const int nr = L > a.n_sink ? (L - a.n_sink) % kG : 0;
+    const int r0 = L - nr;  // first residual row of the prompt
+    const void* src = kind ? a.v : a.k;
+    uint16_t* sink = static_cast<uint16_t*>(kind ? a.c.v_sink : a.c.k_sink) + (size_t)stream * a.n_sink * kD;
+    uint16_t* resid = static_cast<uint16_t*>(kind ? a.c.v_resid : a.c.k_resid) + (size_t)stream * kG * kD;
+    constexpr int U = 4, P = kD / 8;  // pieces of 8 channels
+    const int n = (ns + nr) * P;
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * kThreads) {
+        uint4 w[U];
+        if (a.x_bf16) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(i0 + u * kThreads, n - 1), t = i / P;
+                const size_t row = (size_t)(a.cu[b] + (t < ns ? t : r0 + (t - ns))) * a.c.n_kv + kh;
+                w[u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + row * kD + 8 * (i % P));
+            }
+        } else {
+            float4 lo[U], hi[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(i0 + u * kThreads, n - 1), t = i / P;
+                const size_t row = (size_t)(a.cu[b] + (t < ns ? t : r0 + (t - ns))) * a.c.n_kv + kh;
+                const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(src) + row * kD + 8 * (i % P));
+                lo[u] = p[0];
+                hi[u] = p[1];
+            }
+            auto pair = [](float x, float y) { return (uint32_t)f32_to_bf16(x) | ((uint32_t)f32_to_bf16(y) << 16); };
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                w[u] = make_uint4(pair(lo[u].x, lo[u].y), pair(lo[u].z, lo[u].w), pair(hi[u].x, hi[u].y), pair(hi[u].z, hi[u].w));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kThreads, t = i / P;
+            if (i >= n) break;
+            uint16_t* dst = t < ns ? sink + (size_t)t * kD : resid + (size_t)(t - ns) * kD;
+            *reinterpret_cast<uint4*>(dst + 8 * (i % P)) = w[u];
+        }
+    }
+}
+
+// One workgroup per (sequence, kv head, K|V, body tile), which quantizes the prompt's tile straight
+// from the packed rows (token stride n_kv * 128 elements), then one per (sequence, kv head, K|V) for
+// the rows that stay bf16: these fill the tail of the tiles' last round.
 template <bool COMPACT, bool EXACT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_prefill_tiles(PrefillArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_prefill(PrefillArgs a) {
     __shared__ QuantSmem sm;
+    if ((int64_t)blockIdx.x >= a.tile_blocks) {
+        const int64_t c = (int64_t)blockIdx.x - a.tile_blocks;
+        prefill_copy(a, c >> 1, (int)(c & 1));
+        return;
+    }
     const int blk = (int)(blockIdx.x % a.groups);
     const int64_t rest = blockIdx.x / a.groups;
     const int kind = (int)(rest & 1);
@@ -837,45 +898,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     const char* src = static_cast<const char*>(kind ? a.v : a.k) + (size_t)((row * a.c.n_kv + kh) * kD) * esz;
     uint8_t* dst = static_cast<uint8_t*>(kind ? a.c.v_body : a.c.k_body) + (size_t)ti * tile_bytes(a.P.bits, COMPACT);
     quantize_tile<COMPACT, EXACT>(src, a.x_bf16 != 0, (int64_t)a.c.n_kv * kD, kind, a.P, dst, nullptr, sm);
-}
-
-// One workgroup per (sequence, kv head): sink and residual rows as bf16, then seq_len.
-__global__ __launch_bounds__(kThreads) void k_prefill_copy(PrefillArgs a) {
-    const int64_t stream = blockIdx.x;
-    const int b = (int)(stream / a.c.n_kv), kh = (int)(stream % a.c.n_kv);
-    const int L = prefill_len(a, b);
-    if (threadIdx.x == 0 && kh == 0) {
-        a.c.seq_len[b] = L < 0 ? 0 : L;
-        if (L < 0 && a.c.err_word)
-            __hip_atomic_fetch_or(a.c.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (L < 0) return;
-    const int ns = min(L, a.n_sink);
-    const int nr = L > a.n_sink ? (L - a.n_sink) % kG : 0;
-    const int r0 = L - nr;  // first residual row of the prompt
-    // rows [0, ns) -> sink, rows [r0, L) -> residual; 2 rows of 128 channels per pass
-    for (int i = threadIdx.x; i < (ns + nr) * kD; i += kThreads) {
-        const int t = i / kD, c = i % kD;
-        const int row = t < ns ? t : r0 + (t - ns);
-        const size_t at = ((size_t)(a.cu[b] + row) * a.c.n_kv + kh) * kD + c;
-        uint16_t kb, vb;
-        if (a.x_bf16) {
-            kb = static_cast<const uint16_t*>(a.k)[at];
-            vb = static_cast<const uint16_t*>(a.v)[at];
-        } else {
-            kb = f32_to_bf16(static_cast<const float*>(a.k)[at]);
-            vb = f32_to_bf16(static_cast<const float*>(a.v)[at]);
-        }
-        if (t < ns) {
-            const size_t o = ((size_t)stream * a.n_sink + t) * kD + c;
-            static_cast<uint16_t*>(a.c.k_sink)[o] = kb;
-            static_cast<uint16_t*>(a.c.v_sink)[o] = vb;
-        } else {
-            const size_t o = ((size_t)stream * kG + (t - ns)) * kD + c;
-            static_cast<uint16_t*>(a.c.k_resid)[o] = kb;
-            static_cast<uint16_t*>(a.c.v_resid)[o] = vb;
-        }
-    }
 }
 
 }  // namespace
@@ -911,21 +933,15 @@ hipError_t launch_prefill(const QParams& qp, const kvarn_cache& c, int n_sink, c
     const bool exact = exact_quotient(qp);
     int groups = max_len > n_sink ? (max_len - n_sink) / kG : 0;
     if (groups > c.max_blocks) groups = c.max_blocks;
-    PrefillArgs a{qp, c, n_sink, k, v, x_bf16 ? 1 : 0, cu_seqlens, max_len, groups > 0 ? groups : 1};
-    const int64_t streams = (int64_t)c.batch * c.n_kv;
-    if (groups > 0) {
-        const int64_t n = streams * 2 * groups;
-        if (n >= (int64_t)1 << 31) return hipErrorInvalidValue;
-        if (qp.compact)
-            hipLaunchKernelGGL((k_prefill_tiles<true, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-        else if (exact)
-            hipLaunchKernelGGL((k_prefill_tiles<false, true>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-        else
-            hipLaunchKernelGGL((k_prefill_tiles<false, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_prefill_copy, dim3((unsigned)streams), dim3(kThreads), 0, stream, a);
+    const int64_t streams = (int64_t)c.batch * c.n_kv, tiles = streams * 2 * groups, n = tiles + streams * 2;
+    if (tiles >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    PrefillArgs a{qp, c, n_sink, k, v, x_bf16 ? 1 : 0, cu_seqlens, max_len, groups, tiles};
+    if (qp.compact)
+        hipLaunchKernelGGL((k_prefill<true, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
+    else if (exact)
+        hipLaunchKernelGGL((k_prefill<false, true>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_prefill<false, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
