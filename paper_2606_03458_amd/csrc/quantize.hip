@@ -2,10 +2,19 @@
 // Algorithm 1), asymmetric RTN (Sec. 2.1, Eq. 1) and bit-packing with the dual-scale aux of
 // App. D.  One 256-thread workgroup quantizes one 128-token x 128-channel tile held entirely
 // in registers: thread (tr, tc) owns tokens 8*tr..8*tr+7 and channels 8*tc..8*tc+7, with
-// tc = lane % 16 (a DPP row of 16 lanes spans all 128 channels of a token) and
-// tr = 4*wave + lane / 16.  Row (per-token) reductions stay inside a 16-lane row; column
+// tc the channel block of lane % 16 (a DPP row of 16 lanes spans all 128 channels of a token)
+// and tr = 4*wave + lane / 16.  Row (per-token) reductions stay inside a 16-lane row; column
 // (per-channel) reductions cross the four 16-lane groups of a wave and then the four waves
 // through LDS, in a fixed order so that every thread sees bit-identical results.
+//
+// Bound by the vector ALU, whose instructions are not equal on gfx950 (measured per SIMD with four
+// waves): a plain fp32 add, multiply or multiply-add issues every 2.4 cycles, a max, min, byte permute,
+// conversion or any lane move every 4.3, a row swap or a transcendental every 8.2.  Half of a VarN
+// iteration is its 384 multiply-adds; so sums go as reduce-scatters, statistics are kept by the one lane
+// that owns a row or column, and lane moves are folded into the arithmetic.  65536 x 16384-element
+// key tiles from bf16 at 2 bits: 32768 tiles 1445 us (every lane all sums, rotation stages through the
+// LDS crossbar, IEEE divisions) -> 1235 us, 866 -> 1015 GB/s; 4099 value tiles from fp32 at 4 bits,
+// compact aux, 245 -> 195 us.
 #include <type_traits>
 
 #include "common.hpp"
@@ -16,23 +25,76 @@ namespace {
 constexpr int kThreads = 256;
 
 struct QuantSmem {
-    float red[2][4][kD];          // column partials [buffer][wave][channel]
-    alignas(16) float tot[2][kD];  // column totals [buffer][channel]
-    float rpick[4][4][8];         // row variances of each DPP row [wave][row][token], for the row update
-    float rstat[2][4][2];         // per-wave row max / min [buffer][wave][max, min]
-    alignas(16) uint8_t codes[kG * kD];  // keys: [token][channel]; values: [channel][token]
+    alignas(16) float red[2][4][kD];  // column partials [buffer][wave][channel]
+    alignas(16) float tot[kD];        // column totals
+    float stat[4][4];                 // per-wave partials of the row maximum and minimum, or of the tile shift
+    alignas(16) uint8_t codes[kG * kD];  // keys: [token][channel]; values: [channel][token] (swizzled)
 };
 
+// Lane tc of a DPP row holds channel block cb, channels 8 cb .. 8 cb + 7: cb is tc with its two
+// low bits inverted in the lanes with bit 2 set, so that the lane whose block differs in bit 2 alone is
+// tc ^ 7, the half-row mirror, and every stage of the rotation is one lane move (the others: tc ^ 1, tc
+// ^ 2, and tc ^ 8 as a rotation of the row by 8).
 struct Lane {
-    int tid, lane, wave, tc, tr;
+    int tid, lane, wave, tc, tr, G, cb;
     __device__ Lane() {
         tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // formed anew for each tile of a flush, not held in registers across them
         lane = tid & 63;
         wave = tid >> 6;
         tc = lane & 15;
-        tr = wave * 4 + (lane >> 4);
+        G = lane >> 4;
+        tr = wave * 4 + G;
+        cb = tc & 4 ? tc ^ 3 : tc;
     }
 };
+
+// ---- lane moves folded into arithmetic -------------------------------------------------------
+// x[j] += move(x[j]) * B, and x[j] = min or max(x[j], move(x[j])), for eight values, the lane move folded
+// into the instruction (the compiler emits moves of their own here, with wait states between).  An
+// instruction may read a register through a lane move no sooner than two after it was written: the
+// s_nop covers what came before, the eight values each other.
+#define KVARN_EACH8(OP, TAIL)                                                                          \
+    "s_nop 1\n\t" OP " %0, %0, " TAIL(0) "\n\t" OP " %1, %1, " TAIL(1) "\n\t" OP " %2, %2, " TAIL(2) "\n\t" OP \
+    " %3, %3, " TAIL(3) "\n\t" OP " %4, %4, " TAIL(4) "\n\t" OP " %5, %5, " TAIL(5) "\n\t" OP " %6, %6, " TAIL(6) \
+    "\n\t" OP " %7, %7, " TAIL(7)
+#define KVARN_REGS8 "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
+#define KVARN_ALL " row_mask:0xf bank_mask:0xf"
+template <int M>
+__device__ __forceinline__ void butterfly8(float (&x)[8], float B) {
+#define TAIL1(k) "%8 quad_perm:[1,0,3,2]" KVARN_ALL
+#define TAIL2(k) "%8 quad_perm:[2,3,0,1]" KVARN_ALL
+#define TAIL4(k) "%8 row_half_mirror" KVARN_ALL
+#define TAIL8(k) "%8 row_ror:8" KVARN_ALL
+    if constexpr (M == 1) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL1) : KVARN_REGS8 : "v"(B));
+    else if constexpr (M == 2) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL2) : KVARN_REGS8 : "v"(B));
+    else if constexpr (M == 4) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL4) : KVARN_REGS8 : "v"(B));
+    else asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL8) : KVARN_REGS8 : "v"(B));
+#undef TAIL1
+#undef TAIL2
+#undef TAIL4
+#undef TAIL8
+}
+// Minimum and maximum over the 16 lanes of a row, in every lane.
+#define TAILA(k) "%" #k " quad_perm:[1,0,3,2]" KVARN_ALL
+#define TAILB(k) "%" #k " quad_perm:[2,3,0,1]" KVARN_ALL
+#define TAILC(k) "%" #k " row_half_mirror" KVARN_ALL
+#define TAILD(k) "%" #k " row_mirror" KVARN_ALL
+__device__ __forceinline__ void rows_min8(float (&x)[8]) {
+    asm(KVARN_EACH8("v_min_f32_dpp", TAILA) "\n\t" KVARN_EACH8("v_min_f32_dpp", TAILB) "\n\t" KVARN_EACH8("v_min_f32_dpp", TAILC)
+        "\n\t" KVARN_EACH8("v_min_f32_dpp", TAILD) "\n\ts_nop 1" : KVARN_REGS8);
+}
+__device__ __forceinline__ void rows_max8(float (&x)[8]) {
+    asm(KVARN_EACH8("v_max_f32_dpp", TAILA) "\n\t" KVARN_EACH8("v_max_f32_dpp", TAILB) "\n\t" KVARN_EACH8("v_max_f32_dpp", TAILC)
+        "\n\t" KVARN_EACH8("v_max_f32_dpp", TAILD) "\n\ts_nop 1" : KVARN_REGS8);
+}
+#undef TAILA
+#undef TAILB
+#undef TAILC
+#undef TAILD
+#undef KVARN_EACH8
+#undef KVARN_REGS8
+#undef KVARN_ALL
 
 // ---- reductions ---------------------------------------------------------------------------
 struct OpSum {
@@ -77,19 +139,46 @@ __device__ __forceinline__ float across_rows(float v) {
     return Op::f(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Across the 16 threads that share a channel block (all token blocks): the four rows of the
-// wave, then the four waves through LDS.  Every thread of a channel block ends with the same
-// values.
-// With STAT, the same LDS round also carries one (max, min) pair per wave (xmax, xmin: the
-// wave's values in, the workgroup's out).
-// The four rows of the wave go as a reduce-scatter: permlane16_swap of two different values
-// leaves, in every lane, the even-row and odd-row partials of one of them (rows 0, 2: the first,
-// rows 1, 3: the second), and permlane32_swap of two such words the two half sums; the operands
-// and their order are those of across_rows, so the sums are the same, but no lane computes
-// results it then discards.  Row r of a wave ends with columns 8 tc + r and 8 tc + 4 + r.
-template <class Op, bool STAT = false>
-__device__ __forceinline__ void reduce_cols(float (&s)[8], QuantSmem& sm, int& buf, const Lane& L,
-                                            float* xmax = nullptr, float* xmin = nullptr) {
+// Maximum of mx and minimum of mn over the wave, both >= 0 (their bit patterns order as signed
+// integers), left in lane 63: quad, half-row and row exchanges, then row 0 into row 1 and row 2 into
+// row 3, then row 1 into rows 2 and 3.  Moves and comparisons in one instruction each, at half the
+// rate of an add; a row-pair swap costs twice that.  (Two wait states between an instruction and a
+// lane move of its result: the other chain's instruction and the s_nop.)
+__device__ __forceinline__ void wave_max_min(float& mx, float& mn) {
+    asm("s_nop 1\n\t"
+        "v_max_i32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_i32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_i32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_i32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_i32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_max_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_min_i32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(mx), "+v"(mn));
+}
+__device__ __forceinline__ float lane63(float v) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Column reductions, across the 16 threads that share a channel block (all token blocks): the four
+// rows of the wave here, then the four waves through LDS.  The rows go as a reduce-scatter:
+// permlane16_swap of two different values leaves, in every lane, the even-row and odd-row partials
+// of one of them (rows 0, 2: the first, rows 1, 3: the second), and permlane32_swap of two such words
+// the two half sums, so no lane computes results it then discards.  Row G of a wave ends with columns
+// G and 4 + G of the block's eight, which it writes to red[buf][wave] side by side (column k of the
+// block at 8 tc + 2 (k % 4) + k / 4): consecutive lanes write and read consecutive words.
+template <class Op>
+__device__ __forceinline__ void scatter_cols(const float (&s)[8], QuantSmem& sm, int buf, const Lane& L) {
     float t[4], rr[2];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -101,45 +190,64 @@ __device__ __forceinline__ void reduce_cols(float (&s)[8], QuantSmem& sm, int& b
         const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[2 * k]), __float_as_uint(t[2 * k + 1]), false, false);
         rr[k] = Op::f(__uint_as_float(y[0]), __uint_as_float(y[1]));
     }
-    {
-        const int r = L.lane >> 4;
-        sm.red[buf][L.wave][8 * L.tc + r] = rr[0];
-        sm.red[buf][L.wave][8 * L.tc + 4 + r] = rr[1];
-    }
-    if (STAT && L.lane == 0) {
-        sm.rstat[buf][L.wave][0] = *xmax;
-        sm.rstat[buf][L.wave][1] = *xmin;
-    }
-    __syncthreads();
-    if (STAT) {
-        *xmax = fmax_any(fmax_any(sm.rstat[buf][0][0], sm.rstat[buf][1][0]), fmax_any(sm.rstat[buf][2][0], sm.rstat[buf][3][0]));
-        *xmin = fmin_any(fmin_any(sm.rstat[buf][0][1], sm.rstat[buf][1][1]), fmin_any(sm.rstat[buf][2][1], sm.rstat[buf][3][1]));
-    }
-    // each column's four wave partials are combined once (thread c of the first two waves),
-    // then every thread of the channel block reads its eight totals
+    *reinterpret_cast<float2*>(&sm.red[buf][L.wave][8 * L.tc + 2 * L.G]) = make_float2(rr[0], rr[1]);
+}
+// Each column's four wave partials, combined once (by the first two waves), times scale;
+// every thread of the channel block then reads its eight.  Between scatter_cols and the end two
+// barriers, so the buffer and tot can be written again by the next call.
+template <class Op>
+__device__ __forceinline__ void total_cols(float (&s)[8], float scale, QuantSmem& sm, int buf, const Lane& L) {
     if (L.tid < kD) {
         const int c = L.tid;
-        sm.tot[buf][c] = Op::f(Op::f(Op::f(sm.red[buf][0][c], sm.red[buf][1][c]), sm.red[buf][2][c]), sm.red[buf][3][c]);
+        const float v = Op::f(Op::f(Op::f(sm.red[buf][0][c], sm.red[buf][1][c]), sm.red[buf][2][c]), sm.red[buf][3][c]);
+        sm.tot[c] = v * scale;
     }
     __syncthreads();
-    const float4 lo = *reinterpret_cast<const float4*>(&sm.tot[buf][8 * L.tc]);
-    const float4 hi = *reinterpret_cast<const float4*>(&sm.tot[buf][8 * L.tc + 4]);
-    s[0] = lo.x; s[1] = lo.y; s[2] = lo.z; s[3] = lo.w;
-    s[4] = hi.x; s[5] = hi.y; s[6] = hi.z; s[7] = hi.w;
-    buf ^= 1;
+    const float4 lo = *reinterpret_cast<const float4*>(&sm.tot[8 * L.tc]);
+    const float4 hi = *reinterpret_cast<const float4*>(&sm.tot[8 * L.tc + 4]);
+    s[0] = lo.x; s[4] = lo.y; s[1] = lo.z; s[5] = lo.w;
+    s[2] = hi.x; s[6] = hi.y; s[3] = hi.z; s[7] = hi.w;
 }
 
-// Across the 16 channel-block threads of a token row (one DPP row).
-template <class Op>
-__device__ __forceinline__ void reduce_rows(float (&s)[8]) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = row16<Op>(s[i]);
+// Sum over the 16 lanes of a DPP row of s[tc / 2], as a reduce-scatter (16 instructions against 32
+// for the eight sums in every lane).  Two stages of adds that write part of the row only: the row
+// mirror leaves s[0..3] in lanes 0-7 and s[4..7] in lanes 8-15, the half mirror two of those in
+// the lower and upper quad of each half; then one select and exchange inside the quad.  The
+// instructions read a register through DPP no sooner than two after it was written, inside the
+// block by their order, at its ends by the s_nop.
+__device__ __forceinline__ float scatter_rows(float (&s)[8], const Lane& L) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %5, %5 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %7, %7 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 1"
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])
+        : "v"(s[4]), "v"(s[5]), "v"(s[6]), "v"(s[7]));
+    const bool odd = (L.tc & 2) != 0;
+    float v = odd ? s[1] : s[0];
+    v += dppf<0x4E>(odd ? s[0] : s[1]);
+    return v + dppf<0xB1>(v);
+}
+// The value of token i in every lane of the row, from the lanes 2 i that own it.
+__device__ __forceinline__ void gather_rows(float own, float (&out)[8]) {
+    out[0] = dppf<0x150>(own); out[1] = dppf<0x152>(own); out[2] = dppf<0x154>(own); out[3] = dppf<0x156>(own);
+    out[4] = dppf<0x158>(own); out[5] = dppf<0x15A>(own); out[6] = dppf<0x15C>(own); out[7] = dppf<0x15E>(own);
 }
 
-// Variance over tokens of every column of T*w (two-pass, ddof = 1).  The first LDS round also
-// reduces the wave's (rmax, rmin) of the row variances to the workgroup's.
-__device__ __forceinline__ void column_var(const float (&x)[8][8], const float (&w)[8], float (&var)[8],
-                                           QuantSmem& sm, int& buf, const Lane& L, float& rmax, float& rmin) {
+// Variance over tokens of the columns of T*w (two-pass, ddof = 1) that this lane owns, columns
+// G and 4 + G of its eight.  The means go to every lane; the first LDS round also reduces the wave's
+// (rmax, rmin) of the row variances, in lane 63, to the workgroup's.
+__device__ __forceinline__ void column_var(const float (&x)[8][8], const float (&w)[8], float (&var)[2],
+                                           QuantSmem& sm, const Lane& L, float& rmax, float& rmin) {
     // (explicit fmas: each pass forms x * w inside its own fma)
     float s[8];
 #pragma unroll
@@ -149,10 +257,13 @@ __device__ __forceinline__ void column_var(const float (&x)[8][8], const float (
         for (int i = 0; i < 8; ++i) acc = fmaf(x[i][j], w[i], acc);
         s[j] = acc;
     }
-    reduce_cols<OpSum, true>(s, sm, buf, L, &rmax, &rmin);
+    scatter_cols<OpSum>(s, sm, 0, L);
+    if (L.lane == 63) *reinterpret_cast<float2*>(sm.stat[L.wave]) = make_float2(rmax, rmin);
+    __syncthreads();
+    rmax = fmax_any(fmax_any(sm.stat[0][0], sm.stat[1][0]), fmax_any(sm.stat[2][0], sm.stat[3][0]));
+    rmin = fmin_any(fmin_any(sm.stat[0][1], sm.stat[1][1]), fmin_any(sm.stat[2][1], sm.stat[3][1]));
     float mean[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mean[j] = s[j] * (1.0f / kG);
+    total_cols<OpSum>(mean, 1.0f / kG, sm, 0, L);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         float acc = 0.f;
@@ -163,14 +274,20 @@ __device__ __forceinline__ void column_var(const float (&x)[8][8], const float (
         }
         s[j] = acc;
     }
-    reduce_cols<OpSum>(s, sm, buf, L);
+    scatter_cols<OpSum>(s, sm, 1, L);
+    __syncthreads();
+    // (no second round: the owners read the four wave partials of their two columns themselves)
+    float2 p[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) var[j] = s[j] * (1.0f / (kG - 1));
+    for (int k = 0; k < 4; ++k) p[k] = *reinterpret_cast<const float2*>(&sm.red[1][k][8 * L.tc + 2 * L.G]);
+    var[0] = (((p[0].x + p[1].x) + p[2].x) + p[3].x) * (1.0f / (kG - 1));
+    var[1] = (((p[0].y + p[1].y) + p[2].y) + p[3].y) * (1.0f / (kG - 1));
 }
 
-// Variance over channels of every row of T*u (two-pass, ddof = 1).
-__device__ __forceinline__ void row_var(const float (&x)[8][8], const float (&u)[8], float (&var)[8]) {
-    float s[8];
+// Variance over channels of the row of T*u that this lane owns, token tc / 2 of its eight (two-pass,
+// ddof = 1).
+__device__ __forceinline__ float row_var(const float (&x)[8][8], const float (&u)[8], const Lane& L) {
+    float s[8], mean[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         float acc = 0.f;
@@ -178,10 +295,7 @@ __device__ __forceinline__ void row_var(const float (&x)[8][8], const float (&u)
         for (int j = 0; j < 8; ++j) acc = fmaf(x[i][j], u[j], acc);
         s[i] = acc;
     }
-    reduce_rows<OpSum>(s);
-    float mean[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) mean[i] = s[i] * (1.0f / kD);
+    gather_rows(scatter_rows(s, L) * (1.0f / kD), mean);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         float acc = 0.f;
@@ -192,36 +306,18 @@ __device__ __forceinline__ void row_var(const float (&x)[8][8], const float (&u)
         }
         s[i] = acc;
     }
-    reduce_rows<OpSum>(s);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) var[i] = s[i] * (1.0f / (kD - 1));
+    return scatter_rows(s, L) * (1.0f / (kD - 1));
 }
 
-// Imb of Algorithm 1 from the row variances (per token, replicated over tc) and the column
-// variances (per channel, replicated over tr), in two parts: the wave's max / min of the row
-// variances (reduced over the workgroup by column_var's first LDS round), then the value.
-__device__ __forceinline__ void row_stat(const float (&vr)[8], float& rmax, float& rmin) {
-    rmax = rmin = vr[0];
-#pragma unroll
-    for (int k = 1; k < 8; ++k) {
-        rmax = fmaxf(rmax, vr[k]);
-        rmin = fminf(rmin, vr[k]);
-    }
-    rmax = across_rows<OpMax>(rmax);
-    rmin = across_rows<OpMin>(rmin);
-}
-__device__ __forceinline__ float imbalance(float rmax, float rmin, const float (&vc)[8]) {
-    float cmax = vc[0], cmin = vc[0];
-#pragma unroll
-    for (int k = 1; k < 8; ++k) {
-        cmax = fmaxf(cmax, vc[k]);
-        cmin = fminf(cmin, vc[k]);
-    }
-    // all 128 channels live in one 16-lane row
-    cmax = row16<OpMax>(cmax);
-    cmin = row16<OpMin>(cmin);
+// Imb of Algorithm 1 from the row variances (one token per lane) and the column variances (two
+// channels per lane), in two parts: the wave's max / min of the row variances (reduced over the
+// workgroup by column_var's first LDS round), then the value.
+__device__ __forceinline__ float imbalance(float rmax, float rmin, const float (&vc)[2]) {
+    // all 128 channels live in the wave
+    float cmax = fmax_any(vc[0], vc[1]), cmin = fmin_any(vc[0], vc[1]);
+    wave_max_min(cmax, cmin);
     // (hardware reciprocal, ~1 ulp: Imb only ranks iterations, and values that close are ties)
-    return rmax * __builtin_amdgcn_rcpf(fmaxf(rmin, 1e-8f)) + cmax * __builtin_amdgcn_rcpf(fmaxf(cmin, 1e-8f));
+    return rmax * __builtin_amdgcn_rcpf(fmaxf(rmin, 1e-8f)) + lane63(cmax) * __builtin_amdgcn_rcpf(fmaxf(lane63(cmin), 1e-8f));
 }
 
 __device__ __forceinline__ float clampf(float v, float lo, float hi) { return fminf(fmaxf(v, lo), hi); }
@@ -233,39 +329,24 @@ __device__ __forceinline__ float ln_hw(float v) { return __builtin_amdgcn_logf(v
 __device__ __forceinline__ float exp_hw(float v) { return __builtin_amdgcn_exp2f(v * kLog2e); }
 
 // ---- shared log-scale updates ----------------------------------------------------------------
-// The four lanes of a wave that hold the same eight columns (lanes l, l^16, l^32, l^48) each
-// update two of them, columns 2G and 2G + 1 of the eight (G = lane / 16); the sixteen lanes of
-// a DPP row, which hold the same eight tokens, update token tc % 8.  The results are gathered
-// back into every lane: with equal operands a 16-lane-row swap returns the (even row, odd row)
-// values of a row pair and a half swap the (lower half, upper half) values; a DPP row
-// broadcast returns lane i of the row.
+// Every column and token is updated by the lanes that own it: of the four lanes of a wave that hold
+// the same eight columns (lanes l, l^16, l^32, l^48) each updates columns G and 4 + G of them
+// (G = lane / 16); of the sixteen lanes of a DPP row, which hold the same eight tokens, lane tc
+// updates token tc / 2.  The results are gathered back into every lane: with equal operands a
+// 16-lane-row swap returns the (even row, odd row) values of a row pair and a half swap the (lower
+// half, upper half) values; a DPP row broadcast returns one lane of the row.
 __device__ __forceinline__ void gather_cols(const float (&own)[2], float (&out)[8]) {
     const auto a0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(own[0]), __float_as_uint(own[0]), false, false);
     const auto a1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(own[1]), __float_as_uint(own[1]), false, false);
-    // a0 = (column 2*(G&2), column 2*(G&2) + 2), a1 = the same + 1; the half swap then gives the
-    // values of rows 0-1 and 2-3
-    const auto b0 = __builtin_amdgcn_permlane32_swap(a0[0], a0[0], false, false);  // columns 0, 4
-    const auto b1 = __builtin_amdgcn_permlane32_swap(a0[1], a0[1], false, false);  // columns 2, 6
-    const auto b2 = __builtin_amdgcn_permlane32_swap(a1[0], a1[0], false, false);  // columns 1, 5
-    const auto b3 = __builtin_amdgcn_permlane32_swap(a1[1], a1[1], false, false);  // columns 3, 7
-    out[0] = __uint_as_float(b0[0]); out[4] = __uint_as_float(b0[1]);
-    out[2] = __uint_as_float(b1[0]); out[6] = __uint_as_float(b1[1]);
-    out[1] = __uint_as_float(b2[0]); out[5] = __uint_as_float(b2[1]);
-    out[3] = __uint_as_float(b3[0]); out[7] = __uint_as_float(b3[1]);
-}
-__device__ __forceinline__ void gather_rows(float own, float (&out)[8]) {
-    out[0] = dppf<0x150>(own); out[1] = dppf<0x151>(own); out[2] = dppf<0x152>(own); out[3] = dppf<0x153>(own);
-    out[4] = dppf<0x154>(own); out[5] = dppf<0x155>(own); out[6] = dppf<0x156>(own); out[7] = dppf<0x157>(own);
-}
-// v[2G + q] in lane row G (v the same in the four rows): a row-pair swap of two registers keeps
-// the first one's even rows and moves the second one's even rows into the odd rows; a half swap
-// of two registers keeps the first one's low half and moves the second one's low half up.
-__device__ __forceinline__ float pick_col(const float (&v)[8], int q) {
-    auto p16 = [](float a, float b) {
-        return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)[0]);
-    };
-    const float lo = p16(v[q], v[2 + q]), hi = p16(v[4 + q], v[6 + q]);  // rows: v[q], v[2+q], v[q], v[2+q]
-    return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false)[0]);
+    // row pair P holds (own of row 2P, own of row 2P + 1); the half swap then gives pairs 0 and 1
+    const auto b0 = __builtin_amdgcn_permlane32_swap(a0[0], a0[0], false, false);  // columns 0, 2
+    const auto b1 = __builtin_amdgcn_permlane32_swap(a0[1], a0[1], false, false);  // columns 1, 3
+    const auto b2 = __builtin_amdgcn_permlane32_swap(a1[0], a1[0], false, false);  // columns 4, 6
+    const auto b3 = __builtin_amdgcn_permlane32_swap(a1[1], a1[1], false, false);  // columns 5, 7
+    out[0] = __uint_as_float(b0[0]); out[2] = __uint_as_float(b0[1]);
+    out[1] = __uint_as_float(b1[0]); out[3] = __uint_as_float(b1[1]);
+    out[4] = __uint_as_float(b2[0]); out[6] = __uint_as_float(b2[1]);
+    out[5] = __uint_as_float(b3[0]); out[7] = __uint_as_float(b3[1]);
 }
 
 // ---- narrow formats of the compact aux (App. D: 8-bit float scales, 16-bit float offset) ----
@@ -293,13 +374,23 @@ __device__ __forceinline__ float fp16_round(float x, uint32_t& bits) {
     return (float)h;
 }
 
+// Byte of a code in QuantSmem::codes: rows of 128 bytes, their 16-byte (keys) or 8-byte (values) blocks
+// permuted by the row, and every other eight tokens' rows swapped in pairs, so that neither the writes
+// (8 bytes per lane, a row or a column of blocks at once) nor the gathers of the packing meet a bank
+// more often than their width needs (unswizzled, two thirds of the LDS cycles were conflicts).
+__device__ __forceinline__ int key_code_at(int t, int c) {
+    return (t ^ ((t >> 3) & 1)) * kD + 16 * ((c >> 4) ^ (t & 7)) + (c & 15);
+}
+__device__ __forceinline__ int value_code_at(int c, int t) {
+    return (c ^ ((t >> 3) & 1)) * kG + 8 * ((t >> 3) ^ (c >> 3) ^ ((c & 7) << 1)) + (t & 7);
+}
+
 // Quantize one tile.  src: token t at src + t*tstride elements, channels contiguous (16-byte
 // aligned rows).  dst: the packed tile (16-byte aligned).
 template <bool COMPACT, bool EXACT>
 __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int kind, const QParams& P, uint8_t* dst,
                               int32_t* best_out, QuantSmem& sm) {
     const Lane L;
-    int buf = 0;
     float x[8][8];
 
     // ---- a1: load -------------------------------------------------------------------------
@@ -307,7 +398,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     for (int i = 0; i < 8; ++i) {
         const int64_t t = 8 * L.tr + i;
         if (bf16) {
-            const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + t * tstride + 8 * L.tc);
+            const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + t * tstride + 8 * L.cb);
             const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -315,7 +406,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
                 x[i][2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
             }
         } else {
-            const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(src) + t * tstride + 8 * L.tc);
+            const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(src) + t * tstride + 8 * L.cb);
             const float4 a = p[0], b = p[1];
             x[i][0] = a.x; x[i][1] = a.y; x[i][2] = a.z; x[i][3] = a.w;
             x[i][4] = b.x; x[i][5] = b.y; x[i][6] = b.z; x[i][7] = b.w;
@@ -343,21 +434,17 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
         // a pair and -1 in the upper one: the upper lane then holds -(a - b) instead of a - b.
         // Partners always hold values of the same sign, so the signs stay consistent and every
         // value is exactly +- the butterfly's (round to nearest is symmetric); after the four
-        // stages lane tc holds (-1)^popcount(tc) times it, which the final scaling removes.
+        // stages block cb's lane holds (-1)^popcount(cb) times it, which the final scaling removes.
+        // (channel stride 8 m lives in the lane of block cb ^ m)
 #pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {  // channel stride 8*m lives in lane tc ^ m
-            const float B = (L.tc & m) ? -1.f : 1.f;
+        for (int i = 0; i < 8; ++i) butterfly8<1>(x[i], L.cb & 1 ? -1.f : 1.f);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 8; ++i) butterfly8<2>(x[i], L.cb & 2 ? -1.f : 1.f);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    // partners ^1 and ^2 by DPP quad permutes, ^4 and ^8 through the LDS crossbar
-                    const float p = m == 1 ? dppf<0xB1>(x[i][j]) : (m == 2 ? dppf<0x4E>(x[i][j]) : __shfl_xor(x[i][j], m));
-                    x[i][j] = fmaf(p, B, x[i][j]);
-                }
-            }
-        }
-        const float scale = (__builtin_popcount(L.tc) & 1) ? -kInvSqrt128 : kInvSqrt128;
+        for (int i = 0; i < 8; ++i) butterfly8<4>(x[i], L.cb & 4 ? -1.f : 1.f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) butterfly8<8>(x[i], L.cb & 8 ? -1.f : 1.f);
+        const float scale = (__builtin_popcount(L.cb) & 1) ? -kInvSqrt128 : kInvSqrt128;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
 #pragma unroll
@@ -366,51 +453,39 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     }
 
     // ---- a3/a4: VarN (Algorithm 1), Cur = T * u[c] * w[t] with u = exp(-L_c), w = exp(-L_r) -
-    // Each lane keeps the log-scales it updates (columns 2G, 2G + 1 and token tc % 8 of its
-    // eight, current and best) and all eight scale factors u, w (gathered).
-    const int G = L.lane >> 4, ir = L.tc & 7;
-    float Lc2[2] = {0.f, 0.f}, bLc2[2] = {0.f, 0.f}, uo[2] = {1.f, 1.f};
+    // Each lane keeps the log-scales it updates (columns G, 4 + G and token tc / 2 of its eight,
+    // current and best) and all eight scale factors u, w (gathered).
+    float Lc2[2] = {0.f, 0.f}, bLc2[2] = {0.f, 0.f};
     float Lr1 = 0.f, bLr1 = 0.f, wo = 1.f;
-    float u[8], w[8], cv[8], rv[8];
+    float u[8], w[8], vc[2];
 #pragma unroll
     for (int k = 0; k < 8; ++k) u[k] = w[k] = 1.f;
     float rmax, rmin;
-    row_var(x, u, rv);  // variance over channels of T's rows
-    row_stat(rv, rmax, rmin);
-    column_var(x, w, cv, sm, buf, L, rmax, rmin);  // variance over tokens of T's columns
-    float I_best = imbalance(rmax, rmin, cv);
+    rmax = rmin = row_var(x, u, L);  // variance over channels of T's rows
+    wave_max_min(rmax, rmin);
+    column_var(x, w, vc, sm, L, rmax, rmin);  // variance over tokens of T's columns
+    float I_best = imbalance(rmax, rmin, vc);
     int best = 0;
     for (int k = 1; k <= P.iters; ++k) {
         // column update from the current column variances u^2 * var_t(T w)
+        float uo[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const float v = clampf(uo[q] * uo[q] * pick_col(cv, q), P.var_min, P.var_max);
-            Lc2[q] = clampf(Lc2[q] + 0.5f * ln_hw(v), P.log_lo, P.log_hi);
+            Lc2[q] = clampf(Lc2[q] + 0.5f * ln_hw(clampf(vc[q], P.var_min, P.var_max)), P.log_lo, P.log_hi);
             uo[q] = exp_hw(-Lc2[q]);
         }
         gather_cols(uo, u);
         // row update from the row variances w^2 * var_c(T u)
-        row_var(x, u, rv);
-        {
-            // the row's variances pass through LDS inside the wave to the lane that updates
-            // token ir (LDS operations of a wave complete in order: no barrier)
-            if (L.tc == 0) {
-                *reinterpret_cast<float4*>(&sm.rpick[L.wave][G][0]) = make_float4(rv[0], rv[1], rv[2], rv[3]);
-                *reinterpret_cast<float4*>(&sm.rpick[L.wave][G][4]) = make_float4(rv[4], rv[5], rv[6], rv[7]);
-            }
-            const float v = clampf(wo * wo * sm.rpick[L.wave][G][ir], P.var_min, P.var_max);
-            Lr1 = clampf(Lr1 + 0.5f * ln_hw(v), P.log_lo, P.log_hi);
-            wo = exp_hw(-Lr1);
-        }
+        const float rv = row_var(x, u, L);
+        Lr1 = clampf(Lr1 + 0.5f * ln_hw(clampf(wo * wo * rv, P.var_min, P.var_max)), P.log_lo, P.log_hi);
+        wo = exp_hw(-Lr1);
         gather_rows(wo, w);
-        // imbalance of the new Cur; its column statistics seed the next column update
-        float vr[8], vc[8];
-#pragma unroll
-        for (int m = 0; m < 8; ++m) vr[m] = w[m] * w[m] * rv[m];
-        row_stat(vr, rmax, rmin);
-        column_var(x, w, cv, sm, buf, L, rmax, rmin);
-#pragma unroll
-        for (int m = 0; m < 8; ++m) vc[m] = u[m] * u[m] * cv[m];
+        // imbalance of the new Cur; its column variances seed the next column update
+        rmax = rmin = wo * wo * rv;
+        wave_max_min(rmax, rmin);
+        column_var(x, w, vc, sm, L, rmax, rmin);
+        vc[0] *= uo[0] * uo[0];
+        vc[1] *= uo[1] * uo[1];
         const float I = imbalance(rmax, rmin, vc);
         if (I <= I_best) {  // later iteration wins ties
             I_best = I;
@@ -438,10 +513,19 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
         for (int m = 0; m < 8; ++m)
             s2q[m] = e4m3_round(clampf(kind == KVARN_KEYS ? Sr[m] : Sc[m], 0.015625f, 448.f), false);
+        // T / s2, correctly rounded: the quotient by the rounded reciprocal, corrected once by its exact
+        // remainder (Markstein); a division each is four times as long
+        float inv[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) inv[m] = 1.0f / s2q[m];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[i][j] = x[i][j] / (kind == KVARN_KEYS ? s2q[i] : s2q[j]);
+            for (int j = 0; j < 8; ++j) {
+                const float d = kind == KVARN_KEYS ? s2q[i] : s2q[j], r = kind == KVARN_KEYS ? inv[i] : inv[j];
+                const float q = x[i][j] * r;
+                x[i][j] = fmaf(fmaf(-q, d, x[i][j]), r, q);
+            }
         }
     } else {
 #pragma unroll
@@ -452,7 +536,12 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     }
 
     // ---- a6: RTN along the group axis (keys: per channel, values: per token) ----------------
-    const float qmax = (float)((1 << P.bits) - 1);
+    const float qmax = (float)((1 << P.bits) - 1), inv_qmax = P.bits == 2 ? 1.0f / 3.0f : 1.0f / 15.0f;
+    // x / qmax, correctly rounded (as above)
+    auto over_qmax = [&](float v) {
+        const float q = v * inv_qmax;
+        return fmaf(fmaf(-q, qmax, v), inv_qmax, q);
+    };
     float mn[8], mx[8];
     if (kind == KVARN_KEYS) {
 #pragma unroll
@@ -464,8 +553,12 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
                 mx[j] = fmaxf(mx[j], x[i][j]);
             }
         }
-        reduce_cols<OpMin>(mn, sm, buf, L);
-        reduce_cols<OpMax>(mx, sm, buf, L);
+        scatter_cols<OpMin>(mn, sm, 0, L);
+        __syncthreads();  // (also: every owner is done with red[1] of the last column variances)
+        scatter_cols<OpMax>(mx, sm, 1, L);
+        total_cols<OpMin>(mn, 1.f, sm, 0, L);
+        __syncthreads();  // tot is read
+        total_cols<OpMax>(mx, 1.f, sm, 1, L);
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -476,8 +569,8 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
                 mx[i] = fmaxf(mx[i], x[i][j]);
             }
         }
-        reduce_rows<OpMin>(mn);
-        reduce_rows<OpMax>(mx);
+        rows_min8(mn);
+        rows_max8(mx);
     }
     if constexpr (COMPACT) {
         // Both stored scales are E4M3 (at most 448) while their product is fixed by the data:
@@ -491,7 +584,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             const float so = kind == KVARN_KEYS ? Sr[m] : Sc[m];
-            st[0] = fmaxf(st[0], (mx[m] - mn[m]) / qmax);
+            st[0] = fmaxf(st[0], over_qmax(mx[m] - mn[m]));
             st[1] = fmaxf(st[1], so);
             st[2] = fmaxf(st[2], -so);
         }
@@ -499,13 +592,12 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
         for (int k = 0; k < 3; ++k) st[k] = across_rows<OpMax>(row16<OpMax>(st[k]));
         if (L.lane == 0) {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) sm.red[buf][L.wave][k] = st[k];
+            for (int k = 0; k < 3; ++k) sm.stat[L.wave][k] = st[k];
         }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            st[k] = fmax_any(fmax_any(sm.red[buf][0][k], sm.red[buf][1][k]), fmax_any(sm.red[buf][2][k], sm.red[buf][3][k]));
-        buf ^= 1;
+            st[k] = fmax_any(fmax_any(sm.stat[0][k], sm.stat[1][k]), fmax_any(sm.stat[2][k], sm.stat[3][k]));
         int e = 0;
         if (-st[2] >= 0.015625f)
             while (e < 64 && ldexpf(st[0], -e) > 448.f && ldexpf(st[1], e + 1) <= 448.f) ++e;
@@ -531,7 +623,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     uint32_t abits[8], bbits[8];
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-        const float step = (mx[m] - mn[m]) / qmax;
+        const float step = over_qmax(mx[m] - mn[m]);
         if constexpr (COMPACT) {
             s[m] = step == 0.f ? 1.f : e4m3_round(step, true);
             off[m] = fp16_round(mn[m], bbits[m]);
@@ -540,7 +632,19 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
             s[m] = step == 0.f ? 1.f : step;
             off[m] = mn[m];
         }
-        inv_s[m] = 1.0f / s[m];
+        const float r = __builtin_amdgcn_rcpf(s[m]);  // one Newton step: rounded to within an ulp
+        inv_s[m] = fmaf(fmaf(-s[m], r, 1.f), r, r);
+    }
+    // (steps near the ends of the fp32 range, where the reciprocal or the step is subnormal)
+    float s_lo = s[0], s_hi = s[0];
+#pragma unroll
+    for (int m = 1; m < 8; ++m) {
+        s_lo = fminf(s_lo, s[m]);
+        s_hi = fmaxf(s_hi, s[m]);
+    }
+    if (!(s_lo > 1e-36f && s_hi < 1e36f)) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) inv_s[m] = 1.0f / s[m];
     }
     // codes -> LDS (keys [t][c], values [c][t]), 8 bytes per thread per token / channel.
     // EXACT (unrotated and unbalanced tiles, the KIVI-style ablation, fp32 aux): the tile holds
@@ -575,7 +679,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
                 uint32_t q[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) q[j] = code(x[i][j], j);
-                *reinterpret_cast<uint2*>(&sm.codes[(8 * L.tr + i) * kD + 8 * L.tc]) =
+                *reinterpret_cast<uint2*>(&sm.codes[key_code_at(8 * L.tr + i, 8 * L.cb)]) =
                     make_uint2(pack4(q[0], q[1], q[2], q[3]), pack4(q[4], q[5], q[6], q[7]));
             }
         } else {
@@ -584,7 +688,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
                 uint32_t q[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) q[i] = code(x[i][j], i);
-                *reinterpret_cast<uint2*>(&sm.codes[(8 * L.tc + j) * kG + 8 * L.tr]) =
+                *reinterpret_cast<uint2*>(&sm.codes[value_code_at(8 * L.cb + j, 8 * L.tr)]) =
                     make_uint2(pack4(q[0], q[1], q[2], q[3]), pack4(q[4], q[5], q[6], q[7]));
             }
         }
@@ -613,19 +717,19 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     };
     if constexpr (COMPACT) {
         if (kind == KVARN_KEYS) {
-            if (L.tr == 0) put_group(8 * L.tc);  // per channel
+            if (L.tr == 0) put_group(8 * L.cb);  // per channel
             if (L.tc == 0) put_s2(8 * L.tr);     // per token
         } else {
             if (L.tc == 0) put_group(8 * L.tr);  // per token
-            if (L.tr == 0) put_s2(8 * L.tc);     // per channel
+            if (L.tr == 0) put_s2(8 * L.cb);     // per channel
         }
     } else {
       if (kind == KVARN_KEYS) {
         if (L.tr == 0) {  // per channel: a = s * S_c*, b = mn * S_c*
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                aux[8 * L.tc + j] = s[j] * Sc[j];
-                aux[kD + 8 * L.tc + j] = mn[j] * Sc[j];
+                aux[8 * L.cb + j] = s[j] * Sc[j];
+                aux[kD + 8 * L.cb + j] = mn[j] * Sc[j];
             }
         }
         if (L.tc == 0) {  // s2 per token
@@ -642,7 +746,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
         }
         if (L.tr == 0) {  // s2 per channel
 #pragma unroll
-            for (int j = 0; j < 8; ++j) aux[2 * kD + 8 * L.tc + j] = Sc[j];
+            for (int j = 0; j < 8; ++j) aux[2 * kD + 8 * L.cb + j] = Sc[j];
         }
       }
     }
@@ -660,13 +764,13 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
         if (kind == KVARN_KEYS) {
             const int t = 64 * sigma + 16 * (wsel >> 1) + m;
             const int c0 = 64 * (wsel & 1) + 16 * G4;
-            const uint4 v = *reinterpret_cast<const uint4*>(&sm.codes[t * kD + c0]);
+            const uint4 v = *reinterpret_cast<const uint4*>(&sm.codes[key_code_at(t, c0)]);
             d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
         } else {
             const int c = 16 * wsel + m;
 #pragma unroll
             for (int ss = 0; ss < 4; ++ss)
-                d[ss] = *reinterpret_cast<const uint32_t*>(&sm.codes[c * kG + 64 * sigma + 16 * ss + 4 * G4]);
+                d[ss] = *reinterpret_cast<const uint32_t*>(&sm.codes[value_code_at(c, 64 * sigma + 16 * ss + 4 * G4)]);
         }
     };
     if (P.bits == 2) {
