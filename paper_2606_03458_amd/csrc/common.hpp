@@ -58,6 +58,7 @@ hipError_t launch_append(const kvarn_cache& c, int n_sink, const void* k_new, co
 struct DecodePlan {
     int n_chunk, g_chunk;  // query heads of a group taken in n_chunk chunks of up to g_chunk (<= 8)
     int n_wg, group;       // workgroups per (sequence, kv head, chunk) and waves per workgroup
+    int order;             // 1: the longest sequences first
     int ws_parts;          // partials per query head that the workspace has room for (n_wg <= ws_parts or n_wg == 1)
 };
 

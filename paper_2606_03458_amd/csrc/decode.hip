@@ -54,6 +54,7 @@ constexpr int kRC = 32;     // bf16 tokens (sink / residual) per chunk
 // Waves of one workgroup at most: one workgroup then fills a CU (three waves per SIMD for the
 // 2-bit kernels of up to four heads, two for the others).
 constexpr int kMaxGroup3 = 12, kMaxGroup2 = 8;
+constexpr int kOrderBatch = 128;  // sequences that a wave ranks by length (two per lane)
 
 // A fixed-point grid is only formed for a maximum above this; below it the values are taken
 // as zero.  For p~ this drops a tile whose probabilities are all below 1e-30 relative to the
@@ -83,6 +84,7 @@ struct DecodeArgs {
     int n_streams;     // batch * n_kv
     int n_chunk, g_chunk;  // head chunks per stream and heads per chunk
     int n_wg, group;   // workgroups per (stream, head chunk), waves per workgroup
+    int order;         // 1: longest sequences first (batch at most kOrderBatch)
     float inv_waves;   // 1 / (n_wg * group)
     float* ws;         // [batch][n_q][n_wg][kPart] when n_wg > 1
     // Fused append of a lock-step step: > 0 the common length of the sequences with the token of
@@ -455,6 +457,32 @@ __device__ __forceinline__ uint32_t rows_digit_reduce_scatter4(uint32_t x0, uint
     return c[0] + (c[1] << 8);
 }
 
+// The sequence with the given rank by length, the longest first (equal ones in order of index).
+// Every wave ranks the whole batch, two sequences per lane; where all are equally long, rank is index.
+__device__ __forceinline__ int sequence_of_rank(const int32_t* seq_len, int batch, int rank, int l) {
+    const int i0 = min(l, batch - 1), i1 = min(64 + l, batch - 1);
+    const int len0 = seq_len[i0], len1 = seq_len[i1];
+    const int first = __builtin_amdgcn_readfirstlane(len0);
+    if (!__any(len0 != first || len1 != first)) return rank;
+    // unique keys: the length (capped, an order is all that is asked), then the smaller index
+    const uint32_t k0 = (uint32_t)min(max(len0, 0), 0xFFFFFF) << 7 | (uint32_t)(kOrderBatch - 1 - i0);
+    const uint32_t k1 = (uint32_t)min(max(len1, 0), 0xFFFFFF) << 7 | (uint32_t)(kOrderBatch - 1 - i1);
+    int r0 = 0, r1 = 0;
+    for (int i = 0; i < min(batch, 64); ++i) {
+        const uint32_t k = __builtin_amdgcn_readlane(k0, i);
+        r0 += k > k0;
+        r1 += k > k1;
+    }
+    for (int i = 64; i < batch; ++i) {
+        const uint32_t k = __builtin_amdgcn_readlane(k1, i - 64);
+        r0 += k > k0;
+        r1 += k > k1;
+    }
+    // (clamped lanes repeat the last sequence; the first lane that holds the rank is taken)
+    const uint64_t m0 = __ballot(r0 == rank), m1 = __ballot(r1 == rank);
+    return min(m0 ? __builtin_ctzll(m0) : 64 + __builtin_ctzll(m1), batch - 1);
+}
+
 // X1 = 1 (group size 5, with NH = 1): a fifth query head spread over the whole wave instead of a
 // second head group of four slots, carried by the head group's own products in the digit slot
 // the group leaves empty: q~ and p~ have three digits, so A row 4 h + 3 (slot 3 of head h) is
@@ -492,9 +520,14 @@ void k_decode4(DecodeArgs a) {
     const int wgi = a.n_wg > 1 ? blockIdx.x % a.n_wg : 0;
     const int cs = a.n_wg > 1 ? blockIdx.x / a.n_wg : blockIdx.x;
     const int chunk = a.n_chunk > 1 ? cs / a.n_streams : 0;
-    const int stream = cs - chunk * a.n_streams;
+    int stream = cs - chunk * a.n_streams;
     const int g = min(a.g_chunk, a.g - chunk * a.g_chunk);  // query heads of this wave
-    const int b = stream / a.n_kv, kvh = stream % a.n_kv;
+    int b = stream / a.n_kv;
+    const int kvh = stream - b * a.n_kv;
+    if (a.order) {
+        b = sequence_of_rank(a.seq_len, a.n_streams / a.n_kv, b, l);
+        stream = b * a.n_kv + kvh;
+    }
     // A fused append takes the step's length from the host (the stored one is read later, off the
     // wave's path, and only checked).
     int len = a.step_len;
@@ -1291,36 +1324,38 @@ DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_len, int 
     p.ws_parts = workspace_parts(streams, nb, max_len, n_sink, per_simd);
     const int units = nb + (std::min(n_sink, std::max(max_len, 0)) + kRC - 1) / kRC + kG / kRC;
     // Waves per workgroup: a CU holds per_cu waves, and a workgroup merges its waves' parts in LDS.
-    // The lines below were measured with 8 kv heads, every plan in turn (us at 2 bits, group size 4
-    // unless said otherwise).
+    // The lines below were measured with 8 kv heads, every plan in turn; times in us at 2 bits, group
+    // size 4 unless said otherwise; "ragged": lengths from a 16th to all of the tokens named.
     p.n_wg = 1;
-    if (streams > 768) {
+    // More workgroups than CUs: the longest sequences go first, so that no long one starts when the
+    // others are done (ragged 384 streams at 16k tokens: 58 -> 50).  Ranking a ragged batch costs a wave
+    // up to 3 us, so only where a sequence may hold 32 tiles or more.
+    p.order = streams > 256 && batch > 1 && batch <= kOrderBatch && nb >= 32;
+    if (streams > 1024 || (streams > 768 && !(p.order && per_simd == 3))) {
         // enough streams to fill the card with one or two waves each (16k tokens: 1024 streams 231 /
-        // 226 / 229 with 1 / 2 / 4 waves, 2048 streams 446 / 490 / 453)
+        // 226 / 229 with 1 / 2 / 4 waves, 2048 streams 446 / 490 / 453; group size 5 276 / 244 / 246)
         p.group = 2 * streams <= 1024LL * per_simd ? 2 : 1;
     } else if (streams > 256) {
-        // Four waves, one per SIMD, so that two workgroups share a CU (512 streams, 1.1k tokens: 23 / 21
-        // / 28 / 30 with 3 / 4 / 6 / 12 waves; groups that are not a multiple of four load the SIMDs
-        // unevenly).  Long sequences take a whole CU in turn: level or up to 4 % slower where all are
-        // equally long, a fifth faster where lengths differ (384 streams of 1k to 16k tokens: 73 with
-        // 4 waves, 58 with 12), since a sequence then takes as long as its own tiles.
-        p.group = nb >= 96 ? per_cu : 4;
+        // Four waves, one per SIMD, so that workgroups share a CU (512 streams, 1.1k tokens: 23 / 21 / 28
+        // / 30 with 3 / 4 / 6 / 12 waves; groups that are not a multiple of four load the SIMDs
+        // unevenly; ragged 1024 streams at 16k: 136 with 2, 101 with 4).  Long sequences of few streams
+        // take a whole CU in turn (384 streams at 16k: 4 % slower where all are equally long, ragged 67
+        // with 4 waves, 50 with 12), since a sequence then takes as long as its own tiles.
+        p.group = streams <= 512 && nb * per_simd >= 192 ? per_cu : 4;
     } else {
         // A CU or more per stream.  Few units: eight waves of one or two units each (8 streams, 1k
         // tokens: 9.5 / 7.9 / 8.8 with 4 / 8 / 12 waves); more: all the CU's waves (2k tokens: 12.4 /
         // 10.2 / 10.0).
         p.group = units <= 16 ? std::min(8, units) : per_cu;
-        // Several workgroups per stream cost a merge launch (about 4 us) and pay once they take some
-        // 20 units off each workgroup (8 streams, 2k tokens: 10.0 alone, 10.0 to 11 shared; 4k: 15.1 alone,
-        // 11.0 shared; 128 streams, 4k: 16.5 and 16.8, 16k: 43 and 39).
-        const int per_wg = p.g_chunk > 5 ? 2 : 4;
-        const int n = std::min({(int)(256 / std::max(streams, 1LL)), (units + per_wg - 1) / per_wg, p.ws_parts});
-        if (n > 1 && (long long)units * (n - 1) > 20LL * n) {
-            // one wave per SIMD unless more shorten the longest wave's run of tiles (32 streams, 16k
-            // tokens: 18.0 / 16.8 / 18.8 with 4 / 6 / 12 waves in 8 workgroups)
-            const int more = per_simd == 3 ? 6 : 8;
+        // Several workgroups of four waves per stream, as many as fill the card with waves or leave
+        // each a unit per wave: they cost a merge launch (about 4 us) and pay by the units they take off the
+        // CU, less what the card's memory rate then allows (8 streams: 2k tokens 10.0 alone and shared,
+        // 4k 15.1 and 11.0; 64 streams: 4k 15.4 and 14.3, 8k 24.8 and 17.6; 128 streams: 4k 15.8 and 17.9, 8k
+        // 25.4 and 24.2, ragged 24.0 and 19.3; 192 streams: 8k 28.2 and 33.4).
+        const int n = std::min({(int)(256 * per_simd / std::max(streams, 1LL)), (units + 3) / 4, 32, p.ws_parts});
+        if (n > 1 && units * (512 - 3 * streams) > 7680) {
             p.n_wg = n;
-            p.group = (nb + n * more - 1) / (n * more) < (nb + n * 4 - 1) / (n * 4) ? more : 4;
+            p.group = 4;
         }
     }
     return p;
@@ -1357,6 +1392,7 @@ hipError_t launch_decode(const kvarn_cache& c, int bits, int compact, int rotate
     a.scale_log2 = sm_scale * kLog2e;
     a.n_wg = plan.n_wg;
     a.group = plan.group;
+    a.order = step ? 0 : plan.order;  // (a lock-step batch is equally long)
     a.inv_waves = 1.f / (float)(plan.n_wg * plan.group);
     a.n_streams = c.batch * c.n_kv;
     a.n_chunk = plan.n_chunk;

@@ -17,11 +17,13 @@ pytestmark = pytest.mark.gpu
     (2, 10, 2, 4, 1, 40, 9),     # 15 units, 8 waves, the extra-head kernel
     (4, 32, 8, 2, 0, 0, 13),     # 17 units, the CU's 12 waves
     (4, 64, 8, 2, 1, 0, 13),     # 17 units, the CU's 8 waves (two head groups)
-    (4, 32, 8, 2, 0, 0, 33),     # 8 workgroups of 6 waves, merged
-    (1, 32, 8, 2, 1, 128, 65),   # 19 workgroups of 4 waves, merged by four waves per head
-    (16, 64, 8, 4, 0, 0, 38),    # 2 workgroups of 8 waves
+    (4, 32, 8, 2, 0, 0, 33),     # 10 workgroups of 4 waves, merged by four waves per head
+    (1, 32, 8, 2, 1, 128, 65),   # 19 workgroups
+    (16, 64, 8, 4, 0, 0, 61),    # 4 workgroups, merged by one wave per head
     (129, 8, 2, 2, 0, 0, 5),     # 258 streams: 4 waves
     (129, 8, 2, 2, 1, 0, 96),    # 258 long streams: 12 waves
+    (100, 12, 3, 2, 0, 0, 65),   # 300 long streams, the longest sequences first (a batch above a wave)
+    (33, 80, 8, 2, 0, 20, 34),   # 528 streams (two head chunks): 4 waves, the longest first
     (400, 8, 2, 2, 0, 7, 3),     # 800 streams: 2 waves
 ])
 def test_decode_plan_edges(batch, n_q, n_kv, bits, aux, n_sink, tiles):
