@@ -245,13 +245,13 @@ KVARN_API int kvarn_decode_attention(const kvarn_params *p, const kvarn_cache *c
  *   host_len_before  required: the length of every sequence before the call (seq_len on the
  *           device must hold it).
  *   workspace  as for kvarn_decode_attention with max_len_hint = host_len_before + 1.
- * When the token goes to the residual without filling it, is bf16 and k_new, v_new are 16-byte
- * aligned, the append runs inside the decode launch: the wave that attends the residual's last
- * chunk reads the new row from k_new / v_new and stores it into the residual, and seq_len is
- * set to host_len_before + 1 without the decode reading it; one launch instead of two.  A
- * sequence whose seq_len is not host_len_before is then left unchanged and bit 2 of err_word
- * is set (its output is not meaningful).  Otherwise (a sink token, a flush, fp32 tokens) the
- * call runs the two entry points' kernels in turn.
+ * When the token goes to the residual without filling it, k_new, v_new are 16-byte aligned and the
+ * token is bf16 or the body dense, the append runs inside the decode launch: the wave that attends
+ * the residual's last chunk reads the new row from k_new / v_new and stores it into the residual,
+ * and seq_len is set to host_len_before + 1 without the decode reading it; one launch instead of
+ * two.  A sequence whose seq_len is not host_len_before is then left unchanged and bit 2 of err_word
+ * is set (its output is not meaningful).  Otherwise (a sink token, a flush, fp32 tokens of a paged
+ * cache) the call runs the two entry points' kernels in turn.
  * Errors: those of both entry points, all checked before anything is enqueued; KVARN_EINVAL for
  * host_len_before < 0 or = INT32_MAX.
  */

@@ -280,8 +280,9 @@ int kvarn_append_decode(const kvarn_params* p, const kvarn_cache* cache, const v
     st = decode_check(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, host_len_before + 1, &workspace,
                       workspace_bytes, false, &plan);
     if (st) return st;
-    if (kv_dtype == KVARN_BF16 && host_len_before >= p->n_sink && !flush && aligned(k_new, 16) && aligned(v_new, 16)) {
-        const StepAppend step{host_len_before, k_new, v_new};
+    if (host_len_before >= p->n_sink && !flush && aligned(k_new, 16) && aligned(v_new, 16) &&
+        (kv_dtype == KVARN_BF16 || !cache->block_table)) {
+        const StepAppend step{host_len_before, k_new, v_new, kv_dtype == KVARN_F32};
         return decode_launch(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, plan, workspace, stream, &step);
     }
     hipError_t e = launch_append(*cache, p->n_sink, k_new, v_new, kv_dtype == KVARN_BF16, stream);

@@ -64,35 +64,38 @@ constexpr int kOrderBatch = 128;  // sequences that a wave ranks by length (two 
 constexpr float kTinyMax = 1e-30f;
 
 struct DecodeArgs {
+    // asked for at once at the start of the kernel (see there)
     const uint8_t* k_body;
     const uint8_t* v_body;
-    uint16_t* k_resid;  // written only by a fused append (step_len > 0)
+    const void* q;
+    int32_t* seq_len;   // read, and written only by a fused append
+    // Fused append of a lock-step step: step_len > 0 is the common length of the sequences with the
+    // token of k_new / v_new ([batch][n_kv][kD], bf16 or fp32) appended as their last residual row;
+    // 0: lengths from seq_len and no append.
+    const void* k_new;
+    const void* v_new;
+    float* ws;         // [batch][n_q][n_wg][kPart] when n_wg > 1
+    void* out;
+    int step_len;
+    int n_wg, group;   // workgroups per (stream, head chunk), waves per workgroup
+    float inv_waves;   // 1 / (n_wg * group)
+    int n_streams;     // batch * n_kv
+    int n_chunk, g_chunk;  // head chunks per stream and heads per chunk
+    int order;         // 1: longest sequences first (batch at most kOrderBatch)
+    int n_kv, n_q, g, max_blocks, n_sink;
+    int q_bf16, out_bf16;
+    int rotate;        // 1: body tiles hold the Hadamard-rotated domain; 0: unrotated (ablations)
+    float scale_log2;  // sm_scale * log2(e): logits are kept in log2 units
+    int new_f32;
+    int n_rows;        // batch * n_q
+    // the rest
+    uint16_t* k_resid;  // written only by a fused append
     uint16_t* v_resid;
     const uint16_t* k_sink;
     const uint16_t* v_sink;
-    int32_t* seq_len;   // read, and written only by a fused append
-    const void* q;
-    int q_bf16;
-    void* out;
-    int out_bf16;
-    int n_kv, n_q, g, max_blocks, n_sink;
-    int rotate;        // 1: body tiles hold the Hadamard-rotated domain; 0: unrotated (ablations)
     const int32_t* block_table;  // paged body: [batch][max_blocks] pool block ids, or null (dense)
-    int n_phys;                  // pool size in blocks (paged)
     uint32_t* err_word;
-    float scale_log2;  // sm_scale * log2(e): logits are kept in log2 units
-    int n_streams;     // batch * n_kv
-    int n_chunk, g_chunk;  // head chunks per stream and heads per chunk
-    int n_wg, group;   // workgroups per (stream, head chunk), waves per workgroup
-    int order;         // 1: longest sequences first (batch at most kOrderBatch)
-    float inv_waves;   // 1 / (n_wg * group)
-    float* ws;         // [batch][n_q][n_wg][kPart] when n_wg > 1
-    // Fused append of a lock-step step: > 0 the common length of the sequences with the token of
-    // k_new / v_new ([batch][n_kv][kD] bf16) appended as their last residual row; 0: lengths
-    // from seq_len and no append.
-    int step_len;
-    const uint16_t* k_new;
-    const uint16_t* v_new;
+    int n_phys;                  // pool size in blocks (paged)
 };
 
 __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
@@ -492,7 +495,9 @@ __device__ __forceinline__ int sequence_of_rank(const int32_t* seq_len, int batc
 // so that lane (G, n) holds the head's logits for tokens 64 sg + 16 G + n and its outputs for
 // channels 16 (4 q + G) + n (sg, q = 0, 1): two values per lane, no padded head slots and no
 // MFMA of its own.
-template <int BITS, int NH, int CMP, int PG, int X1>
+// NEW32 = 1: the fused step's token is fp32.  (Kernels of their own, for dense bodies: as a branch of
+// the others its code costs a short bf16 step 1 to 10 %.)
+template <int BITS, int NH, int CMP, int PG, int X1, int NEW32>
 __global__ __launch_bounds__(64 * (BITS == 2 && NH == 1 && !X1 ? kMaxGroup3 : kMaxGroup2))
 __attribute__((amdgpu_waves_per_eu(BITS == 2 && NH == 1 && !X1 ? 3 : 2, 8)))
 void k_decode4(DecodeArgs a) {
@@ -517,12 +522,19 @@ void k_decode4(DecodeArgs a) {
     // workgroup = (head chunk, stream, part of the stream), the chunk slowest: the chunks of a
     // stream read the same tiles, n_streams * n_wg workgroups apart, which keeps them on one XCD
     // when that distance is a multiple of 8.
-    const int wgi = a.n_wg > 1 ? blockIdx.x % a.n_wg : 0;
-    const int cs = a.n_wg > 1 ? blockIdx.x / a.n_wg : blockIdx.x;
-    const int chunk = a.n_chunk > 1 ? cs / a.n_streams : 0;
-    int stream = cs - chunk * a.n_streams;
+    // Every argument of the set-up is asked for here, in one round of scalar loads: fetched where it is
+    // first used, each line of them costs the wave a miss of its own (the steps of one sequence at 8k
+    // tokens 11.65 -> 11.2 us, of 64 at 1k 15.9 -> 15.3).
+    asm volatile("" ::"s"(a.k_body), "s"(a.v_body), "s"(a.q), "s"(a.seq_len), "s"(a.k_new), "s"(a.v_new), "s"(a.ws), "s"(a.out),
+                 "s"(a.step_len), "s"(a.n_wg), "s"(a.group), "s"(a.inv_waves), "s"(a.n_streams), "s"(a.n_chunk), "s"(a.g_chunk),
+                 "s"(a.order), "s"(a.n_kv), "s"(a.n_q), "s"(a.g), "s"(a.max_blocks), "s"(a.n_sink), "s"(a.q_bf16),
+                 "s"(a.out_bf16), "s"(a.rotate), "s"(a.scale_log2), "s"(a.new_f32));
+    const uint32_t cs = a.n_wg > 1 ? blockIdx.x / (uint32_t)a.n_wg : blockIdx.x;
+    const int wgi = (int)(blockIdx.x - cs * (uint32_t)a.n_wg);
+    const int chunk = a.n_chunk > 1 ? (int)(cs / (uint32_t)a.n_streams) : 0;
+    int stream = (int)(cs - (uint32_t)chunk * (uint32_t)a.n_streams);
     const int g = min(a.g_chunk, a.g - chunk * a.g_chunk);  // query heads of this wave
-    int b = stream / a.n_kv;
+    int b = (int)((uint32_t)stream / (uint32_t)a.n_kv);
     const int kvh = stream - b * a.n_kv;
     if (a.order) {
         b = sequence_of_rank(a.seq_len, a.n_streams / a.n_kv, b, l);
@@ -974,10 +986,11 @@ void k_decode4(DecodeArgs a) {
             const uint16_t* Kp = (in_sink ? a.k_sink : a.k_resid) + row0 * kD;
             const uint16_t* Vp = (in_sink ? a.v_sink : a.v_resid) + row0 * kD;
             // A fused append's token is the residual's last row (of the last chunk): read from
-            // the input, and stored into the residual below.
-            const bool new_row = a.step_len > 0 && c == nch - 1;
-            const uint16_t* Klast = new_row ? a.k_new + (size_t)stream * kD : Kp + (size_t)(cn - 1) * kD;
-            const uint16_t* Vlast = new_row ? a.v_new + (size_t)stream * kD : Vp + (size_t)(cn - 1) * kD;
+            // the input (an fp32 one is rounded and put in the row's place below), and stored into the
+            // residual below.
+            const bool new_row = a.step_len > 0 && c == nch - 1, new_bf16 = new_row && !NEW32;
+            const uint16_t* Klast = new_bf16 ? static_cast<const uint16_t*>(a.k_new) + (size_t)stream * kD : Kp + (size_t)(cn - 1) * kD;
+            const uint16_t* Vlast = new_bf16 ? static_cast<const uint16_t*>(a.v_new) + (size_t)stream * kD : Vp + (size_t)(cn - 1) * kD;
             // Rows past the chunk read its last row (in bounds) and are masked (p = 0).
             v8bf B[2][4];  // key rows 16 tau + n, channels 32 k + 8 G ..
 #pragma unroll
@@ -993,6 +1006,25 @@ void k_decode4(DecodeArgs a) {
             uint32_t v2[kRC];  // value row t, channels 2 l, 2 l + 1
 #pragma unroll
             for (int t = 0; t < kRC; ++t) v2[t] = reinterpret_cast<const uint32_t*>(t < cn - 1 ? Vp + (size_t)t * kD : Vlast)[l];
+            uint32_t new_k = 0, new_v = 0;  // NEW32: the new row's channels 2 l, 2 l + 1
+            if (NEW32 && new_row) {
+                auto pair = [](float2 x) { return (uint32_t)f32_to_bf16(x.x) | (uint32_t)f32_to_bf16(x.y) << 16; };
+                new_k = pair(reinterpret_cast<const float2*>(static_cast<const float*>(a.k_new) + (size_t)stream * kD)[l]);
+                new_v = pair(reinterpret_cast<const float2*>(static_cast<const float*>(a.v_new) + (size_t)stream * kD)[l]);
+                wave_sync();  // the previous chunk is done with sm.p
+                uint32_t* row = reinterpret_cast<uint32_t*>(&sm.p[0][0]);
+                row[l] = new_k;
+                wave_sync();
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v8bf x;
+                    __builtin_memcpy(&x, row + 16 * k + 4 * G, 16);
+#pragma unroll
+                    for (int tau = 0; tau < 2; ++tau) B[tau][k] = 16 * tau + n < cn - 1 ? B[tau][k] : x;
+                }
+#pragma unroll
+                for (int t = 0; t < kRC; ++t) v2[t] = t < cn - 1 ? v2[t] : new_v;
+            }
             if (new_row && chunk == 0) {
                 // The token into the residual (one head chunk writes it), and the step's length (kv
                 // head 0 of the sequence writes it).  The stored length must be the one before the
@@ -1000,8 +1032,8 @@ void k_decode4(DecodeArgs a) {
                 // sequence is left as it is and bit 2 of err_word is set.
                 const int stored = __hip_atomic_load(a.seq_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (stored == a.step_len - 1 || stored == a.step_len) {
-                    reinterpret_cast<uint32_t*>(a.k_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Klast)[l];
-                    reinterpret_cast<uint32_t*>(a.v_resid + (row0 + cn - 1) * kD)[l] = reinterpret_cast<const uint32_t*>(Vlast)[l];
+                    reinterpret_cast<uint32_t*>(a.k_resid + (row0 + cn - 1) * kD)[l] = NEW32 ? new_k : reinterpret_cast<const uint32_t*>(Klast)[l];
+                    reinterpret_cast<uint32_t*>(a.v_resid + (row0 + cn - 1) * kD)[l] = NEW32 ? new_v : reinterpret_cast<const uint32_t*>(Vlast)[l];
                     if (kvh == 0 && l == 0) __hip_atomic_store(a.seq_len + b, a.step_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } else if (l == 0 && a.err_word) {
                     __hip_atomic_fetch_or(a.err_word, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1108,20 +1140,22 @@ void k_decode4(DecodeArgs a) {
     __syncthreads();
     const float rs = a.rotate ? kInvSqrt128 : 1.f;
     for (int hh = wave; hh < g; hh += a.group) {
-        float M = -INFINITY;
-        for (int w = 0; w < a.group; ++w) M = fmaxf(M, part(w)[XM + hh]);
-        float L = 0.f, acc[2] = {0.f, 0.f}, pl[2] = {0.f, 0.f};
+        // lane w: the weight of wave w's part (waves past the last repeat it and count for nothing)
+        const float m = part(min(l, a.group - 1))[XM + hh];
+        const float lw = l < a.group ? part(min(l, a.group - 1))[XL + hh] : 0.f;
+        const float M = wave_max(m);
+        const float ww = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+        const float L = wave_sum(ww * lw);
+        float acc[2] = {0.f, 0.f}, pl[2] = {0.f, 0.f};
         for (int w = 0; w < a.group; ++w) {
             const float* xb = part(w);
-            const float m = xb[XM + hh];
-            const float ww = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+            const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ww), w));
             const float2 x = *reinterpret_cast<const float2*>(xb + hh * kD + 2 * l);
             const float2 y = *reinterpret_cast<const float2*>(xb + XP + hh * kD + 2 * l);
-            L = fmaf(ww, xb[XL + hh], L);
-            acc[0] = fmaf(ww, x.x, acc[0]);
-            acc[1] = fmaf(ww, x.y, acc[1]);
-            pl[0] = fmaf(ww, y.x, pl[0]);
-            pl[1] = fmaf(ww, y.y, pl[1]);
+            acc[0] = fmaf(wt, x.x, acc[0]);
+            acc[1] = fmaf(wt, x.y, acc[1]);
+            pl[0] = fmaf(wt, y.x, pl[0]);
+            pl[1] = fmaf(wt, y.y, pl[1]);
         }
         if (a.n_wg > 1) {
             float* P = a.ws + ((qrow + hh) * a.n_wg + wgi) * kPart;
@@ -1158,9 +1192,10 @@ __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
     const int l = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = wv % W;
+    asm volatile("" ::"s"(a.ws), "s"(a.out), "s"(a.n_wg), "s"(a.n_rows), "s"(a.out_bf16), "s"(a.rotate));  // (one round of scalar loads)
     const size_t bh = (size_t)blockIdx.x * HPB + wv / W;
     // W > 1: one head per workgroup, so every wave leaves here or none does.
-    if (bh >= (size_t)a.n_streams / a.n_kv * a.n_q) return;
+    if (bh >= (size_t)a.n_rows) return;
     const float* P = a.ws + bh * a.n_wg * kPart;
     const int S = a.n_wg;
     // Log-sum-exp over this wave's splits, U of them with every load in flight (indices past the
@@ -1264,19 +1299,11 @@ hipError_t launch_cfg(const DecodeArgs& a, int batch, hipStream_t stream) {
     const int wpg = a.group;
     const dim3 grid((unsigned)(streams * a.n_chunk * a.n_wg)), block(64 * wpg);
     const bool pg = a.block_table != nullptr;
-    if constexpr (GQ == 4) {
-        const size_t lds = wpg * sizeof(Smem4<1, 0>);
-        if (pg) hipLaunchKernelGGL((k_decode4<BITS, 1, CMP, 1, 0>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((k_decode4<BITS, 1, CMP, 0, 0>), grid, block, lds, stream, a);
-    } else if constexpr (GQ == 5) {
-        const size_t lds = wpg * sizeof(Smem4<1, 1>);
-        if (pg) hipLaunchKernelGGL((k_decode4<BITS, 1, CMP, 1, 1>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((k_decode4<BITS, 1, CMP, 0, 1>), grid, block, lds, stream, a);
-    } else if constexpr (GQ == 8) {
-        const size_t lds = wpg * sizeof(Smem4<2, 0>);
-        if (pg) hipLaunchKernelGGL((k_decode4<BITS, 2, CMP, 1, 0>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((k_decode4<BITS, 2, CMP, 0, 0>), grid, block, lds, stream, a);
-    }
+    constexpr int NH = GQ == 8 ? 2 : 1, X1 = GQ == 5 ? 1 : 0;
+    const size_t lds = wpg * sizeof(Smem4<NH, X1>);
+    if (pg) hipLaunchKernelGGL((k_decode4<BITS, NH, CMP, 1, X1, 0>), grid, block, lds, stream, a);
+    else if (a.new_f32) hipLaunchKernelGGL((k_decode4<BITS, NH, CMP, 0, X1, 1>), grid, block, lds, stream, a);
+    else hipLaunchKernelGGL((k_decode4<BITS, NH, CMP, 0, X1, 0>), grid, block, lds, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_wg == 1) return e;
     const size_t heads = (size_t)batch * a.n_q;
@@ -1395,12 +1422,14 @@ hipError_t launch_decode(const kvarn_cache& c, int bits, int compact, int rotate
     a.order = step ? 0 : plan.order;  // (a lock-step batch is equally long)
     a.inv_waves = 1.f / (float)(plan.n_wg * plan.group);
     a.n_streams = c.batch * c.n_kv;
+    a.n_rows = c.batch * n_q;
     a.n_chunk = plan.n_chunk;
     a.g_chunk = plan.g_chunk;
     a.ws = ws;
     a.step_len = step ? step->len_before + 1 : 0;
-    a.k_new = step ? static_cast<const uint16_t*>(step->k_new) : nullptr;
-    a.v_new = step ? static_cast<const uint16_t*>(step->v_new) : nullptr;
+    a.new_f32 = step && step->f32;
+    a.k_new = step ? step->k_new : nullptr;
+    a.v_new = step ? step->v_new : nullptr;
     if (compact) return bits == 2 ? launch_bits<2, 1>(a, c.batch, stream) : launch_bits<4, 1>(a, c.batch, stream);
     return bits == 2 ? launch_bits<2, 0>(a, c.batch, stream) : launch_bits<4, 0>(a, c.batch, stream);
 }
