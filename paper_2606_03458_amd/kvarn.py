@@ -45,6 +45,7 @@ class kvarn_cache(ctypes.Structure):
 
 
 _lib = None
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def library_path() -> str:
@@ -101,6 +102,9 @@ def _ptr(t) -> int | None:
 def _stream(stream) -> int | None:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
+    # the handle itself: building a torch Stream object for it takes 2.8 us of an 8.5 us call
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
