@@ -58,7 +58,7 @@ struct Lane {
     "s_nop 1\n\t" OP " %0, %0, " TAIL(0) "\n\t" OP " %1, %1, " TAIL(1) "\n\t" OP " %2, %2, " TAIL(2) "\n\t" OP \
     " %3, %3, " TAIL(3) "\n\t" OP " %4, %4, " TAIL(4) "\n\t" OP " %5, %5, " TAIL(5) "\n\t" OP " %6, %6, " TAIL(6) \
     "\n\t" OP " %7, %7, " TAIL(7)
-#define KVARN_REGS8 "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
+#define KVARN_REGS8 "+&v"(x[0]), "+&v"(x[1]), "+&v"(x[2]), "+&v"(x[3]), "+&v"(x[4]), "+&v"(x[5]), "+&v"(x[6]), "+&v"(x[7])
 #define KVARN_ALL " row_mask:0xf bank_mask:0xf"
 template <int M>
 __device__ __forceinline__ void butterfly8(float (&x)[8], float B) {
@@ -164,7 +164,7 @@ __device__ __forceinline__ void wave_max_min(float& mx, float& mn) {
         "v_max_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
         "v_min_i32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
         "s_nop 1"
-        : "+v"(mx), "+v"(mn));
+        : "+&v"(mx), "+&v"(mn));
 }
 __device__ __forceinline__ float lane63(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
@@ -230,7 +230,7 @@ __device__ __forceinline__ float scatter_rows(float (&s)[8], const Lane& L) {
         "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
         "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
         "s_nop 1"
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])
+        : "+&v"(s[0]), "+&v"(s[1]), "+&v"(s[2]), "+&v"(s[3])
         : "v"(s[4]), "v"(s[5]), "v"(s[6]), "v"(s[7]));
     const bool odd = (L.tc & 2) != 0;
     float v = odd ? s[1] : s[0];
@@ -1037,16 +1037,27 @@ hipError_t launch_prefill(const QParams& qp, const kvarn_cache& c, int n_sink, c
     const bool exact = exact_quotient(qp);
     int groups = max_len > n_sink ? (max_len - n_sink) / kG : 0;
     if (groups > c.max_blocks) groups = c.max_blocks;
-    const int64_t streams = (int64_t)c.batch * c.n_kv, tiles = streams * 2 * groups, n = tiles + streams * 2;
+    const int64_t streams = (int64_t)c.batch * c.n_kv, tiles = streams * 2 * groups, copies = streams * 2;
     if (tiles >= (int64_t)1 << 31) return hipErrorInvalidValue;
     PrefillArgs a{qp, c, n_sink, k, v, x_bf16 ? 1 : 0, cu_seqlens, max_len, groups, tiles};
-    if (qp.compact)
-        hipLaunchKernelGGL((k_prefill<true, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-    else if (exact)
-        hipLaunchKernelGGL((k_prefill<false, true>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL((k_prefill<false, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
-    return hipGetLastError();
+    auto launch = [&](int64_t n) {
+        if (qp.compact)
+            hipLaunchKernelGGL((k_prefill<true, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
+        else if (exact)
+            hipLaunchKernelGGL((k_prefill<false, true>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
+        else
+            hipLaunchKernelGGL((k_prefill<false, false>), dim3((unsigned)n), dim3(kThreads), 0, stream, a);
+        return hipGetLastError();
+    };
+    // A launch has at most 2^32 - 1 threads: where the tiles alone fit and the copies no longer do, they
+    // go in a launch of their own.
+    if (tiles > 0 && tiles + copies > 0xFFFFFFFFll / kThreads) {
+        const hipError_t e = launch(tiles);
+        if (e != hipSuccess) return e;
+        a.tile_blocks = 0;
+        return launch(copies);
+    }
+    return launch(tiles + copies);
 }
 
 hipError_t launch_flush(const QParams& qp, const kvarn_cache& c, int n_sink, bool all_due, hipStream_t stream) {
