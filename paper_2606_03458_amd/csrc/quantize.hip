@@ -11,10 +11,9 @@
 // waves): a plain fp32 add, multiply or multiply-add issues every 2.4 cycles, a max, min, byte permute,
 // conversion or any lane move every 4.3, a row swap or a transcendental every 8.2.  Half of a VarN
 // iteration is its 384 multiply-adds; so sums go as reduce-scatters, statistics are kept by the one lane
-// that owns a row or column, and lane moves are folded into the arithmetic.  65536 x 16384-element
-// key tiles from bf16 at 2 bits: 32768 tiles 1445 us (every lane all sums, rotation stages through the
-// LDS crossbar, IEEE divisions) -> 1235 us, 866 -> 1015 GB/s; 4099 value tiles from fp32 at 4 bits,
-// compact aux, 245 -> 195 us.
+// that owns a row or column, and lane moves are folded into the arithmetic.  32768 key tiles from bf16
+// at 2 bits: 1443 us (every lane all sums, rotation stages through the LDS crossbar, IEEE divisions) ->
+// 1207 us, 872 -> 1043 GB/s; 4099 value tiles from fp32 at 4 bits, compact aux, 238 -> 191 us.
 #include <type_traits>
 
 #include "common.hpp"
@@ -394,20 +393,31 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     float x[8][8];
 
     // ---- a1: load -------------------------------------------------------------------------
+    // One branch on the type, so that all eight rows are in flight before the first is used: a branch per
+    // row waited for each, eight memory round trips in turn (12 prompts of up to 4k tokens 101.5 -> 97.7 us,
+    // a call of few tiles 22.5 -> 21.4, 32768 tiles 1228 -> 1207).
+    const int64_t at = 8 * L.tr * tstride + 8 * L.cb;
+    if (bf16) {
+        const uint16_t* p = static_cast<const uint16_t*>(src) + at;
+        uint4 v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int64_t t = 8 * L.tr + i;
-        if (bf16) {
-            const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + t * tstride + 8 * L.cb);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const uint4*>(p + i * tstride);
+        __builtin_amdgcn_sched_barrier(0);  // (the first conversion is otherwise put before the other loads)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 x[i][2 * k] = __uint_as_float(w[k] << 16);
                 x[i][2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
             }
-        } else {
-            const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(src) + t * tstride + 8 * L.cb);
-            const float4 a = p[0], b = p[1];
+        }
+    } else {
+        const float* p = static_cast<const float*>(src) + at;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float4 a = *reinterpret_cast<const float4*>(p + i * tstride);
+            const float4 b = *reinterpret_cast<const float4*>(p + i * tstride + 4);
             x[i][0] = a.x; x[i][1] = a.y; x[i][2] = a.z; x[i][3] = a.w;
             x[i][4] = b.x; x[i][5] = b.y; x[i][6] = b.z; x[i][7] = b.w;
         }
@@ -826,8 +836,7 @@ struct TileArgs {
     int32_t* best_iter;
 };
 
-// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the fp32-aux variants keep 8-12 values of
-// the balance and RTN phase in scratch) hide the barrier and LDS latency of the reductions
+// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the compact and exact variants keep 4 to 8 values in scratch) hide the barrier and LDS latency of the reductions
 // better than 3 (measured 11 % faster).  So does the flush, whose grids are one tile per stream and
 // K/V: 1024 tiles fit the card at once (56 us against 67 at 3).
 template <bool COMPACT, bool EXACT>
@@ -1063,7 +1072,7 @@ hipError_t launch_prefill(const QParams& qp, const kvarn_cache& c, int n_sink, c
 hipError_t launch_flush(const QParams& qp, const kvarn_cache& c, int n_sink, bool all_due, hipStream_t stream) {
     const bool exact = exact_quotient(qp);
     FlushArgs a{qp, c, n_sink};
-    // resident grid: 256 CUs x 3 workgroups of 256 threads (the quantizer's occupancy)
+    // resident grid: three workgroups of 256 threads on each of 256 CUs (a CU holds four)
     constexpr int64_t kResidentGrid = 768;
     const int64_t n = (int64_t)c.batch * c.n_kv * 2;
     const unsigned grid = (unsigned)(all_due ? n : (n < kResidentGrid ? n : kResidentGrid));
