@@ -28,10 +28,10 @@
 // of loads, LDS exchanges and products is exposed (one tile takes 1.45 us alone, 0.25 us per CU with
 // twelve waves), and a few waves over a long sequence of a ragged batch last longer than the rest
 // of the card.  Against at most four waves, fixed spans of tiles and one wave finishing alone: one
-// layer of 32 sequences at 32k tokens, compact aux, 131 -> 103 us; 48 sequences of 1k to 16k
-// tokens 84 -> 58 us; a step of 64 sequences at 1k tokens 19.6 -> 15.8 us.  Streams with too few
+// layer of 32 sequences at 32k tokens, compact aux, 131 -> 102 us; 48 sequences of 1k to 16k
+// tokens 84 -> 50 us; a step of 64 sequences at 1k tokens 19.5 -> 15.0 us.  Streams with too few
 // workgroups to fill the card take several, whose partials the merge kernel combines (a step of
-// one sequence at 8k tokens 13.8 -> 11.4 us: 17 partials per head instead of 37).
+// one sequence at 8k tokens 13.9 -> 10.7 us: 17 partials per head instead of 37).
 //
 // A lock-step decode step can append its token in the same launch (Fig. 4): the new row is the
 // residual's last, read from the token input by the wave that attends that chunk, which also
