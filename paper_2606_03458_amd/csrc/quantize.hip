@@ -30,10 +30,11 @@ struct QuantSmem {
     alignas(16) uint8_t codes[kG * kD];  // keys: [token][channel]; values: [channel][token] (swizzled)
 };
 
-// Lane tc of a DPP row holds channel block cb, channels 8 cb .. 8 cb + 7: cb is tc with its two
-// low bits inverted in the lanes with bit 2 set, so that the lane whose block differs in bit 2 alone is
-// tc ^ 7, the half-row mirror, and every stage of the rotation is one lane move (the others: tc ^ 1, tc
-// ^ 2, and tc ^ 8 as a rotation of the row by 8).
+// Lane tc of a DPP row holds channel block cb, channels 8 cb .. 8 cb + 7, such that the lanes whose
+// blocks differ in bit 0, 1, 2 or 3 alone are tc ^ 15 (the row mirror), tc ^ 7 (the half-row mirror),
+// tc ^ 2 and tc ^ 1.  Every stage of the rotation is then one lane move, and the stages of scatter_rows
+// add neighbouring blocks, then neighbouring pairs, quads and halves: a sum's terms are grouped by their
+// channels, so the statistics, and with them the stored tiles, do not change with the order of the lanes.
 struct Lane {
     int tid, lane, wave, tc, tr, G, cb;
     __device__ Lane() {
@@ -44,7 +45,8 @@ struct Lane {
         tc = lane & 15;
         G = lane >> 4;
         tr = wave * 4 + G;
-        cb = tc & 4 ? tc ^ 3 : tc;
+        const int b2 = (tc >> 2) & 1, b3 = tc >> 3;
+        cb = b3 | (b3 ^ b2) << 1 | (((tc >> 1) & 1) ^ b2) << 2 | ((tc & 1) ^ b2) << 3;
     }
 };
 
@@ -61,10 +63,10 @@ struct Lane {
 #define KVARN_ALL " row_mask:0xf bank_mask:0xf"
 template <int M>
 __device__ __forceinline__ void butterfly8(float (&x)[8], float B) {
-#define TAIL1(k) "%8 quad_perm:[1,0,3,2]" KVARN_ALL
-#define TAIL2(k) "%8 quad_perm:[2,3,0,1]" KVARN_ALL
-#define TAIL4(k) "%8 row_half_mirror" KVARN_ALL
-#define TAIL8(k) "%8 row_ror:8" KVARN_ALL
+#define TAIL1(k) "%8 row_mirror" KVARN_ALL
+#define TAIL2(k) "%8 row_half_mirror" KVARN_ALL
+#define TAIL4(k) "%8 quad_perm:[2,3,0,1]" KVARN_ALL
+#define TAIL8(k) "%8 quad_perm:[1,0,3,2]" KVARN_ALL
     if constexpr (M == 1) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL1) : KVARN_REGS8 : "v"(B));
     else if constexpr (M == 2) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL2) : KVARN_REGS8 : "v"(B));
     else if constexpr (M == 4) asm(KVARN_EACH8("v_fmac_f32_dpp", TAIL4) : KVARN_REGS8 : "v"(B));
