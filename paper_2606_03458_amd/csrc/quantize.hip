@@ -329,6 +329,14 @@ __device__ __forceinline__ float clampf(float v, float lo, float hi) { return fm
 __device__ __forceinline__ float ln_hw(float v) { return __builtin_amdgcn_logf(v) * 0.6931471805599453f; }
 __device__ __forceinline__ float exp_hw(float v) { return __builtin_amdgcn_exp2f(v * kLog2e); }
 
+// x / d, correctly rounded, from r = the rounded 1 / d: the product, corrected once by its exact
+// remainder (Markstein).  The remainder is formed as q d - x, so that a zero keeps the sign that the
+// division gives it (the offset of a group is stored with its sign).
+__device__ __forceinline__ float quotient(float x, float d, float r) {
+    const float q = x * r;
+    return fmaf(-fmaf(q, d, -x), r, q);
+}
+
 // ---- shared log-scale updates ----------------------------------------------------------------
 // Every column and token is updated by the lanes that own it: of the four lanes of a wave that hold
 // the same eight columns (lanes l, l^16, l^32, l^48) each updates columns G and 4 + G of them
@@ -525,8 +533,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
         for (int m = 0; m < 8; ++m)
             s2q[m] = e4m3_round(clampf(kind == KVARN_KEYS ? Sr[m] : Sc[m], 0.015625f, 448.f), false);
-        // T / s2, correctly rounded: the quotient by the rounded reciprocal, corrected once by its exact
-        // remainder (Markstein); a division each is four times as long
+        // T / s2, a division each being four times as long
         float inv[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m) inv[m] = 1.0f / s2q[m];
@@ -535,8 +542,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float d = kind == KVARN_KEYS ? s2q[i] : s2q[j], r = kind == KVARN_KEYS ? inv[i] : inv[j];
-                const float q = x[i][j] * r;
-                x[i][j] = fmaf(fmaf(-q, d, x[i][j]), r, q);
+                x[i][j] = quotient(x[i][j], d, r);
             }
         }
     } else {
@@ -549,11 +555,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 
     // ---- a6: RTN along the group axis (keys: per channel, values: per token) ----------------
     const float qmax = (float)((1 << P.bits) - 1), inv_qmax = P.bits == 2 ? 1.0f / 3.0f : 1.0f / 15.0f;
-    // x / qmax, correctly rounded (as above)
-    auto over_qmax = [&](float v) {
-        const float q = v * inv_qmax;
-        return fmaf(fmaf(-q, qmax, v), inv_qmax, q);
-    };
+    auto over_qmax = [&](float v) { return quotient(v, qmax, inv_qmax); };
     float mn[8], mx[8];
     if (kind == KVARN_KEYS) {
 #pragma unroll

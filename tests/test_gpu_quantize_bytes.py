@@ -34,8 +34,13 @@ def _data(name):
     x = _bell(N * 128 * 128, 1).reshape(N, 128, 128)
     channel = 1 + (_hash(N * 128, 2) % np.uint64(64)).astype(np.float64).reshape(N, 1, 128) / 8
     token = 1 + (_hash(N * 128, 3) % np.uint64(64)).astype(np.float64).reshape(N, 128, 1) / 16
-    assert name == "spread"
-    x = x * channel * token
+    if name == "spread":
+        x = x * channel * token
+    elif name == "zeros":  # zeros of both signs with a few values among them, and constant tiles
+        x = x * channel * (_hash(x.size, 4) % np.uint64(50) == 0).reshape(x.shape)
+        x[N // 2:] = np.linspace(-2.0, 2.0, N // 2).reshape(-1, 1, 1)
+    else:
+        raise ValueError(name)
     return x.astype(np.float32)
 
 
