@@ -286,8 +286,8 @@ __device__ __forceinline__ void column_var(const float (&x)[8][8], const float (
 }
 
 // Variance over channels of the row of T*u that this lane owns, token tc / 2 of its eight (two-pass,
-// ddof = 1).
-__device__ __forceinline__ float row_var(const float (&x)[8][8], const float (&u)[8], const Lane& L) {
+// ddof = 1); mean_out: its mean.
+__device__ __forceinline__ float row_var(const float (&x)[8][8], const float (&u)[8], const Lane& L, float* mean_out = nullptr) {
     float s[8], mean[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -296,7 +296,9 @@ __device__ __forceinline__ float row_var(const float (&x)[8][8], const float (&u
         for (int j = 0; j < 8; ++j) acc = fmaf(x[i][j], u[j], acc);
         s[i] = acc;
     }
-    gather_rows(scatter_rows(s, L) * (1.0f / kD), mean);
+    const float own = scatter_rows(s, L) * (1.0f / kD);
+    if (mean_out) *mean_out = own;
+    gather_rows(own, mean);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         float acc = 0.f;
@@ -329,11 +331,13 @@ __device__ __forceinline__ float clampf(float v, float lo, float hi) { return fm
 __device__ __forceinline__ float ln_hw(float v) { return __builtin_amdgcn_logf(v) * 0.6931471805599453f; }
 __device__ __forceinline__ float exp_hw(float v) { return __builtin_amdgcn_exp2f(v * kLog2e); }
 
+constexpr float kMaxF32 = 3.402823466e38f;
+
 // x / d, correctly rounded, from r = the rounded 1 / d: the product, corrected once by its exact
 // remainder (Markstein).  The remainder is formed as q d - x, so that a zero keeps the sign that the
-// division gives it (the offset of a group is stored with its sign).
-__device__ __forceinline__ float quotient(float x, float d, float r) {
-    const float q = x * r;
+// division gives it (the offset of a group is stored with its sign).  The product x r must be finite (an
+// infinite one would make the correction inf - inf).
+__device__ __forceinline__ float corrected_quotient(float x, float d, float q, float r) {
     return fmaf(-fmaf(q, d, -x), r, q);
 }
 
@@ -480,8 +484,11 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
     float u[8], w[8], vc[2];
 #pragma unroll
     for (int k = 0; k < 8; ++k) u[k] = w[k] = 1.f;
-    float rmax, rmin;
-    rmax = rmin = row_var(x, u, L);  // variance over channels of T's rows
+    float rmax, rmin, row_mean;
+    rmax = rmin = row_var(x, u, L, &row_mean);  // variance over channels of T's rows
+    // Whether a value of the wave's rows may pass 1.2e30 (a value is within 12 deviations of its row's
+    // mean), so that a quotient by a stored scale, 2^-6 or more, may pass the fp32 range.
+    const bool huge_x = COMPACT && __any(!(fabsf(row_mean) < 1e30f && rmax < 1e30f));
     wave_max_min(rmax, rmin);
     column_var(x, w, vc, sm, L, rmax, rmin);  // variance over tokens of T's columns
     float I_best = imbalance(rmax, rmin, vc);
@@ -533,7 +540,16 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
         for (int m = 0; m < 8; ++m)
             s2q[m] = e4m3_round(clampf(kind == KVARN_KEYS ? Sr[m] : Sc[m], 0.015625f, 448.f), false);
-        // T / s2, a division each being four times as long
+        // T / s2, a division each being four times as long.  Huge values are divided at a 2^8-th of their
+        // size and scaled up again, so that a quotient beyond the fp32 range is the infinity that the
+        // division gives (a step of that size is stored as the largest scale).
+        if (huge_x) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[i][j] = 0x1p-8f * (fabsf(x[i][j]) > kMaxF32 ? copysignf(kMaxF32, x[i][j]) : x[i][j]);
+            }
+        }
         float inv[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m) inv[m] = 1.0f / s2q[m];
@@ -542,7 +558,14 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float d = kind == KVARN_KEYS ? s2q[i] : s2q[j], r = kind == KVARN_KEYS ? inv[i] : inv[j];
-                x[i][j] = quotient(x[i][j], d, r);
+                x[i][j] = corrected_quotient(x[i][j], d, x[i][j] * r, r);
+            }
+        }
+        if (huge_x) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[i][j] *= 0x1p8f;
             }
         }
     } else {
@@ -555,7 +578,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 
     // ---- a6: RTN along the group axis (keys: per channel, values: per token) ----------------
     const float qmax = (float)((1 << P.bits) - 1), inv_qmax = P.bits == 2 ? 1.0f / 3.0f : 1.0f / 15.0f;
-    auto over_qmax = [&](float v) { return quotient(v, qmax, inv_qmax); };
+    auto over_qmax = [&](float v) { return corrected_quotient(v, qmax, fminf(v * inv_qmax, kMaxF32), inv_qmax); };
     float mn[8], mx[8];
     if (kind == KVARN_KEYS) {
 #pragma unroll
@@ -840,8 +863,9 @@ struct TileArgs {
     int32_t* best_iter;
 };
 
-// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the compact and exact variants keep 4 to 8 values in scratch) hide the barrier and LDS latency of the reductions
-// better than 3 (measured 11 % faster).  So does the flush, whose grids are one tile per stream and
+// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the compact and exact variants keep 5 to 9 values in
+// scratch, the others none, one in the flush) hide the barrier and LDS latency of the reductions better
+// than 3 (measured 11 % faster).  So does the flush, whose grids are one tile per stream and
 // K/V: 1024 tiles fit the card at once (56 us against 67 at 3).
 template <bool COMPACT, bool EXACT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_quantize_tiles(TileArgs a) {

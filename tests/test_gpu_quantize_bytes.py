@@ -39,6 +39,8 @@ def _data(name):
     elif name == "zeros":  # zeros of both signs with a few values among them, and constant tiles
         x = x * channel * (_hash(x.size, 4) % np.uint64(50) == 0).reshape(x.shape)
         x[N // 2:] = np.linspace(-2.0, 2.0, N // 2).reshape(-1, 1, 1)
+    elif name == "huge":  # group ranges beyond the largest fp32 number
+        x = x * (3.3e38 / 4)
     else:
         raise ValueError(name)
     return x.astype(np.float32)
@@ -48,7 +50,7 @@ def digest(K, name, kind, bits, aux):
     h = hashlib.sha256()
     x32 = torch.from_numpy(_data(name)).cuda()
     for x in (x32, x32.to(torch.bfloat16)):
-        for rotate in (1, 0):
+        for rotate in (0,) if name == "huge" else (1, 0):  # (rotated, the huge tokens overflow themselves)
             p = K.kvarn_params_init(bits, aux_format=aux, rotate=rotate)
             out = torch.zeros((N, K.kvarn_tile_bytes(p)), dtype=torch.uint8, device="cuda")
             best = torch.zeros(N, dtype=torch.int32, device="cuda")
