@@ -5,11 +5,11 @@
 #include <stdint.h>
 
 #include "kvarn.h"
+#include "plan.hpp"
 
 namespace kvarn {
 
 constexpr int kD = 128;  // head_dim (channels per token)
-constexpr int kG = 128;  // tokens per quantization group / body tile
 constexpr int64_t kMaxStreams = int64_t(1) << 26;  // (sequence, kv head) pairs a cache may hold
 
 // 1/sqrt(128), rounded to fp32.
@@ -55,14 +55,6 @@ hipError_t launch_prefill(const QParams& qp, const kvarn_cache& c, int n_sink, c
 hipError_t launch_append(const kvarn_cache& c, int n_sink, const void* k_new, const void* v_new, bool bf16,
                          hipStream_t stream);
 
-struct DecodePlan {
-    int n_chunk, g_chunk;  // query heads of a group taken in n_chunk chunks of up to g_chunk (<= 8)
-    int n_wg, group;       // workgroups per (sequence, kv head, chunk) and waves per workgroup
-    int order;             // 1: the longest sequences first
-    int ws_parts;          // partials per query head that the workspace has room for (n_wg <= ws_parts or n_wg == 1)
-};
-
-DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_len, int n_sink, int max_blocks);
 size_t decode_workspace_bytes(int batch, int n_q, const DecodePlan& plan);
 
 // A lock-step decode step's token, appended by the decode launch itself (bf16 or fp32 rows
