@@ -198,7 +198,7 @@ int kvarn_prefill(const kvarn_params* p, const kvarn_cache* cache, const void* k
 size_t kvarn_decode_workspace_bytes(const kvarn_params* p, const kvarn_cache* cache, int32_t n_q,
                                     int32_t max_len_hint) {
     if (check_params(p) || !cache || cache->batch <= 0 || cache->n_kv <= 0 || n_q <= 0 || max_len_hint < 0) return 0;
-    const DecodePlan plan = plan_decode(cache->batch, cache->n_kv, n_q, p->bits, max_len_hint, p->n_sink, cache->max_blocks);
+    const DecodePlan plan = plan_decode(cache->batch, cache->n_kv, n_q, p->bits, max_len_hint, p->n_sink, cache->max_blocks, false);
     return decode_workspace_bytes(cache->batch, n_q, plan);
 }
 
@@ -208,9 +208,9 @@ namespace {
 
 // Validation and planning shared by the decode entry points; nothing is enqueued.  ws == nullptr
 // with use_scratch: the partials go to the library's per-device scratch array (*workspace is set
-// to it).
+// to it).  equal: as for plan_decode.
 int decode_check(const kvarn_params* p, const kvarn_cache* cache, int32_t n_q, const void* q, int32_t q_dtype,
-                 const void* out, int32_t out_dtype, float sm_scale, int32_t max_len_hint, void** workspace,
+                 const void* out, int32_t out_dtype, float sm_scale, int32_t max_len_hint, bool equal, void** workspace,
                  size_t workspace_bytes, bool use_scratch, DecodePlan* plan) {
     int st = check_params(p);
     if (st) return st;
@@ -220,7 +220,7 @@ int decode_check(const kvarn_params* p, const kvarn_cache* cache, int32_t n_q, c
     if (check_dtype(q_dtype) || check_dtype(out_dtype)) return KVARN_EINVAL;
     if (!q || !out || !std::isfinite(sm_scale) || max_len_hint < 0) return KVARN_EINVAL;
     if (!aligned(q, 4) || !aligned(out, 8)) return KVARN_EINVAL;
-    *plan = plan_decode(cache->batch, cache->n_kv, n_q, p->bits, max_len_hint, p->n_sink, cache->max_blocks);
+    *plan = plan_decode(cache->batch, cache->n_kv, n_q, p->bits, max_len_hint, p->n_sink, cache->max_blocks, equal);
     const size_t need = decode_workspace_bytes(cache->batch, n_q, *plan);
     if (use_scratch) {
         if (need > KVARN_NOALLOC_SCRATCH_BYTES) return KVARN_EWORKSPACE;
@@ -245,7 +245,7 @@ int decode_impl(const kvarn_params* p, const kvarn_cache* cache, int32_t n_q, co
                 void* out, int32_t out_dtype, float sm_scale, int32_t max_len_hint, void* workspace,
                 size_t workspace_bytes, bool use_scratch, hipStream_t stream) {
     DecodePlan plan;
-    const int st = decode_check(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, max_len_hint, &workspace,
+    const int st = decode_check(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, max_len_hint, false, &workspace,
                                 workspace_bytes, use_scratch, &plan);
     if (st) return st;
     return decode_launch(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, plan, workspace, stream);
@@ -277,7 +277,7 @@ int kvarn_append_decode(const kvarn_params* p, const kvarn_cache* cache, const v
     int st = append_check(p, cache, k_new, v_new, kv_dtype, host_len_before, &flush);
     if (st) return st;
     DecodePlan plan;
-    st = decode_check(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, host_len_before + 1, &workspace,
+    st = decode_check(p, cache, n_q, q, q_dtype, out, out_dtype, sm_scale, host_len_before + 1, true, &workspace,
                       workspace_bytes, false, &plan);
     if (st) return st;
     if (host_len_before >= p->n_sink && !flush && aligned(k_new, 16) && aligned(v_new, 16) &&

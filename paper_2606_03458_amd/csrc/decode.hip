@@ -1347,7 +1347,7 @@ hipError_t launch_decode(const kvarn_cache& c, int bits, int compact, int rotate
     a.scale_log2 = sm_scale * kLog2e;
     a.n_wg = plan.n_wg;
     a.group = plan.group;
-    a.order = step ? 0 : plan.order;  // (a lock-step batch is equally long)
+    a.order = plan.order;
     a.inv_waves = 1.f / (float)(plan.n_wg * plan.group);
     a.n_streams = c.batch * c.n_kv;
     a.n_rows = c.batch * n_q;
