@@ -66,14 +66,15 @@ inline DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_le
         // One wave leaves the longest sequences of a ragged batch alone on the card, and two the second round
         // nearly empty, so four from 16 tiles on (ragged 8k tokens: 1792 streams 142 / 110 / 97 with 1 / 2 / 4
         // waves, equal 206 / 213 / 202, before 120 and 219; 4 bits, 1152 streams: ragged 128 / 115 / 102, before
-        // 113).  Below that the waves' set-up and merge count for more than they share.  Where two waves per
+        // 113).  Below that the waves' set-up and merge count for more than they share (in a
+        // step below 32: 2560 streams at 2k 89 / 93 with 1 / 4).  Where two waves per
         // stream fit the round they are as good on equal lengths (16k tokens, 1024 streams: 226 with 2, 229 with
         // 4), and four only pay at three waves per SIMD and well off the round's end (ragged 1024 streams at
         // 16k: 136 with 2, 101 with 4; 1536 at 8k, equal: 171 and 174).
         if (2 * streams <= round)
             p.group = per_simd == 3 && (streams <= 1024 ? nb >= 32 : streams <= 1472 && nb >= 16) ? 4 : 2;
         else
-            p.group = nb >= 16 || (per_simd == 2 && streams <= 1280 && nb >= 4) ? 4 : 1;
+            p.group = nb >= (equal ? 32 : 16) || (per_simd == 2 && streams <= 1280 && nb >= 4) ? 4 : 1;
     } else if (streams > 256) {
         // Four waves, one per SIMD, so that workgroups share a CU (512 streams, 1.1k tokens: 23 / 21 / 28
         // / 30 with 3 / 4 / 6 / 12 waves; groups that are not a multiple of four load the SIMDs

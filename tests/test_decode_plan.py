@@ -88,7 +88,7 @@ def test_plans_fit_the_card_and_the_workspace(plans):
     # more than 768: as many waves as share the longest sequences of a ragged batch
     (832, 16384, dict(n_kv=1), 1, 4), (832, 3000, dict(n_kv=1), 1, 2), (1024, 16384, dict(bits=4), 1, 2),
     (1152, 2048, dict(), 1, 4), (1152, 1920, dict(), 1, 2), (1472, 2048, dict(), 1, 4), (1480, 8192, dict(), 1, 2), (1536, 8192, dict(), 1, 2), (1544, 8192, dict(), 1, 4),
-    (1544, 1920, dict(), 1, 1), (3064, 8192, dict(), 1, 4), (3072, 8192, dict(), 1, 1),
+    (1544, 1920, dict(), 1, 1), (1544, 2100, dict(), 1, 4), (1544, 2100, dict(equal=1), 1, 1), (3064, 8192, dict(), 1, 4), (3072, 8192, dict(), 1, 1),
     (1152, 600, dict(bits=4), 1, 4), (1152, 511, dict(bits=4), 1, 1), (1288, 600, dict(bits=4), 1, 1), (2040, 4096, dict(group=8), 1, 4),
     (2048, 4096, dict(group=8), 1, 1), (576, 16384, dict(group=16, bits=4), 1, 4),
 ])
