@@ -984,6 +984,9 @@ void k_decode4(DecodeArgs a) {
             const bool new_row = a.step_len > 0 && c == nch - 1, new_bf16 = new_row && !NEW32;
             const uint16_t* Klast = new_bf16 ? static_cast<const uint16_t*>(a.k_new) + (size_t)stream * kD : Kp + (size_t)(cn - 1) * kD;
             const uint16_t* Vlast = new_bf16 ? static_cast<const uint16_t*>(a.v_new) + (size_t)stream * kD : Vp + (size_t)(cn - 1) * kD;
+            // (with the chunk's rows: the check below then waits for no memory round trip of its own)
+            int stored = 0;
+            if (!NEW32 && new_row && chunk == 0) stored = __hip_atomic_load(a.seq_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // Rows past the chunk read its last row (in bounds) and are masked (p = 0).
             v8bf B[2][4];  // key rows 16 tau + n, channels 32 k + 8 G ..
 #pragma unroll
@@ -1023,7 +1026,7 @@ void k_decode4(DecodeArgs a) {
                 // head 0 of the sequence writes it).  The stored length must be the one before the
                 // append, or the one after it (kv head 0 may have stored it already); else the
                 // sequence is left as it is and bit 2 of err_word is set.
-                const int stored = __hip_atomic_load(a.seq_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (NEW32) stored = __hip_atomic_load(a.seq_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (stored == a.step_len - 1 || stored == a.step_len) {
                     reinterpret_cast<uint32_t*>(a.k_resid + (row0 + cn - 1) * kD)[l] = NEW32 ? new_k : reinterpret_cast<const uint32_t*>(Klast)[l];
                     reinterpret_cast<uint32_t*>(a.v_resid + (row0 + cn - 1) * kD)[l] = NEW32 ? new_v : reinterpret_cast<const uint32_t*>(Vlast)[l];
