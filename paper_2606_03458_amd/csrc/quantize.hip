@@ -140,30 +140,30 @@ __device__ __forceinline__ float across_rows(float v) {
     return Op::f(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Maximum of mx and minimum of mn over the wave, both >= 0 (their bit patterns order as signed
-// integers), left in lane 63: quad, half-row and row exchanges, then row 0 into row 1 and row 2 into
-// row 3, then row 1 into rows 2 and 3.  Moves and comparisons in one instruction each, at half the
-// rate of an add; a row-pair swap costs twice that.  (Two wait states between an instruction and a
+// Maximum of mx and minimum of mn over the wave, left in lane 63 (a NaN, the variance of a row or column with
+// a NaN or an infinite value, counts for nothing): quad, half-row and row exchanges, then row 0 into row 1
+// and row 2 into row 3, then row 1 into rows 2 and 3.  Moves and comparisons in one instruction each, at
+// half the rate of an add; a row-pair swap costs twice that.  (Two wait states between an instruction and a
 // lane move of its result: the other chain's instruction and the s_nop.)
 __device__ __forceinline__ void wave_max_min(float& mx, float& mn) {
     asm("s_nop 1\n\t"
-        "v_max_i32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_max_i32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_max_i32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_max_i32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_max_i32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
         "s_nop 0\n\t"
-        "v_max_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-        "v_min_i32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_min_f32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
         "s_nop 1"
         : "+&v"(mx), "+&v"(mn));
 }
@@ -317,7 +317,9 @@ __device__ __forceinline__ float row_var(const float (&x)[8][8], const float (&u
 // workgroup by column_var's first LDS round), then the value.
 __device__ __forceinline__ float imbalance(float rmax, float rmin, const float (&vc)[2]) {
     // all 128 channels live in the wave
-    float cmax = fmax_any(vc[0], vc[1]), cmin = fmin_any(vc[0], vc[1]);
+    float cmax, cmin;
+    asm("v_max_f32 %0, %1, %2" : "=v"(cmax) : "v"(vc[0]), "v"(vc[1]));  // (fmaxf would quiet both first)
+    asm("v_min_f32 %0, %1, %2" : "=v"(cmin) : "v"(vc[0]), "v"(vc[1]));
     wave_max_min(cmax, cmin);
     // (hardware reciprocal, ~1 ulp: Imb only ranks iterations, and values that close are ties)
     return rmax * __builtin_amdgcn_rcpf(fmaxf(rmin, 1e-8f)) + lane63(cmax) * __builtin_amdgcn_rcpf(fmaxf(lane63(cmin), 1e-8f));

@@ -41,6 +41,22 @@ def _data(name):
         x[N // 2:] = np.linspace(-2.0, 2.0, N // 2).reshape(-1, 1, 1)
     elif name == "huge":  # group ranges beyond the largest fp32 number
         x = x * (3.3e38 / 4)
+    elif name == "tiny":  # down to subnormal values and steps
+        x = x * channel * 2.0 ** -(100 + 2 * np.arange(N)).reshape(N, 1, 1)
+    elif name == "infinite":  # one to four infinities in a token, of one sign or both
+        x = x * channel * token
+        for t in range(N):
+            for k in range(1 + t % 4):
+                x[t, 5 * t, (37 * k + 11 * t) % 128] = -np.inf if (t // 4 >> k) & 1 else np.inf
+    elif name == "nan":  # a NaN, infinities of both signs, and a token of many, in 8 tiles each
+        x = x * channel * token
+        i = np.arange(N)
+        x[i[0::3], 5 * i[0::3], 3 * i[0::3] + 1] = np.nan
+        x[i[1::3], 4 * i[1::3], 2] = np.inf
+        x[i[1::3], 127 - i[1::3], 100] = -np.inf
+        many = (_hash(N * 128, 6) % np.uint64(6)).reshape(N, 128)
+        for t in i[2::3]:
+            x[t, 3 * t] = np.select([many[t] == 0, many[t] == 1, many[t] == 2], [np.inf, -np.inf, np.nan], x[t, 3 * t])
     else:
         raise ValueError(name)
     return x.astype(np.float32)
@@ -55,6 +71,9 @@ def digest(K, name, kind, bits, aux):
             out = torch.zeros((N, K.kvarn_tile_bytes(p)), dtype=torch.uint8, device="cuda")
             best = torch.zeros(N, dtype=torch.int32, device="cuda")
             K.kvarn_quantize_block(p, kind, x, K._dtype(x), N, 1, 128 * 128, 0, 128, out, 1, 1, best)
+            if name in ("nan", "infinite") and aux == 0:  # (the sign of a NaN is not a value)
+                scales = out[:, bits * 2048:].view(torch.float32)
+                scales[scales.isnan()] = float("nan")
             h.update(out.cpu().numpy().tobytes())
             h.update(best.cpu().numpy().tobytes())
     return h.hexdigest()
