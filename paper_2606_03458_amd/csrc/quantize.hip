@@ -542,14 +542,15 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
         for (int m = 0; m < 8; ++m)
             s2q[m] = e4m3_round(clampf(kind == KVARN_KEYS ? Sr[m] : Sc[m], 0.015625f, 448.f), false);
-        // T / s2, a division each being four times as long.  Huge values are divided at a 2^8-th of their
+        // T / s2, a division each being four times as long.  Huge values are divided at a 2^16-th of their
         // size and scaled up again, so that a quotient beyond the fp32 range is the infinity that the
-        // division gives (a step of that size is stored as the largest scale).
+        // division gives (a step of that size is stored as the largest scale).  An infinite value is divided
+        // as 2^121, which passes the range for every divisor when it is scaled up.
         if (huge_x) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[i][j] = 0x1p-8f * (fabsf(x[i][j]) > kMaxF32 ? copysignf(kMaxF32, x[i][j]) : x[i][j]);
+                for (int j = 0; j < 8; ++j) x[i][j] = fabsf(x[i][j]) > kMaxF32 ? copysignf(0x1p121f, x[i][j]) : 0x1p-16f * x[i][j];
             }
         }
         float inv[8];
@@ -567,7 +568,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[i][j] *= 0x1p8f;
+                for (int j = 0; j < 8; ++j) x[i][j] *= 0x1p16f;
             }
         }
     } else {
