@@ -101,9 +101,8 @@ __device__ __forceinline__ void rows_max8(float (&x)[8]) {
 struct OpSum {
     __device__ static float f(float a, float b) { return a + b; }
 };
-// Max and min in the NaN-propagating forms: no operand here is a NaN (the input is finite), and
-// fmaxf / fminf would first quiet every operand that comes from another lane or from LDS (one
-// more instruction each).
+// Max and min in the NaN-propagating forms: fmaxf / fminf would first quiet every operand that comes
+// from another lane or from LDS (one more instruction each).
 __device__ __forceinline__ float fmax_any(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 __device__ __forceinline__ float fmin_any(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 struct OpMax {
@@ -607,6 +606,18 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
             for (int j = 1; j < 8; ++j) {
                 mn[i] = fminf(mn[i], x[i][j]);
                 mx[i] = fmaxf(mx[i], x[i][j]);
+            }
+        }
+        // A lane whose eight values are all NaN makes its row's range one; the folded lane moves would pass
+        // over it.  (0 unless a minimum is a NaN or infinite)
+        float odd = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) odd = fmaf(mn[i], 0.f, odd);
+        if (__any(odd != 0.f)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                mn[i] = row16<OpMin>(mn[i]);
+                mx[i] = row16<OpMax>(mx[i]);
             }
         }
         rows_min8(mn);
