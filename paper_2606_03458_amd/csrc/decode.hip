@@ -1295,6 +1295,7 @@ hipError_t launch_cfg(const DecodeArgs& a, int batch, hipStream_t stream) {
     const int wpg = a.group;
     const dim3 grid((unsigned)(streams * a.n_chunk * a.n_wg)), block(64 * wpg);
     const bool pg = a.block_table != nullptr;
+    if (pg && a.new_f32) return hipErrorInvalidValue;  // (no such kernel: the paged ones read the token as bf16)
     constexpr int NH = GQ == 8 ? 2 : 1, X1 = GQ == 5 ? 1 : 0;
     const size_t lds = wpg * sizeof(Smem4<NH, X1>);
     if (pg) hipLaunchKernelGGL((k_decode4<BITS, NH, CMP, 1, X1, 0>), grid, block, lds, stream, a);

@@ -50,18 +50,21 @@ def _same(a, b, what):
 
 
 # (bits, aux, n_q, n_kv, batch, n_sink, context, paged, token dtype): the plans and kernels a
-# step can take
+# step can take (waves of a stream's workgroup, by csrc/plan.hpp)
 CASES = [
-    (2, 0, 32, 8, 96, 0, 6 * 128 + 124, False, "bf16"),     # 768 streams: 3 body splits + a residual split, one workgroup
-    (2, 0, 32, 8, 64, 0, 50 * 128 + 124, False, "bf16"),    # 512 streams: 4 body splits sharing the chunks
-    (2, 0, 32, 8, 3, 100, 20 * 128 + 224, False, "bf16"),   # 24 streams: many splits, residual splits, merge kernel
-    (2, 0, 32, 8, 400, 0, 3 * 128 + 124, False, "bf16"),    # 3200 streams: one split each
+    (2, 0, 32, 8, 96, 0, 6 * 128 + 124, False, "bf16"),     # 768 streams: four waves
+    (2, 0, 32, 8, 64, 0, 50 * 128 + 124, False, "bf16"),    # 512 streams: four waves over a longer body
+    (2, 0, 32, 8, 3, 100, 20 * 128 + 224, False, "bf16"),   # 24 streams: seven workgroups each, merge kernel
+    (2, 0, 32, 8, 400, 0, 3 * 128 + 124, False, "bf16"),    # 3200 streams: one wave each
     (2, 0, 40, 8, 48, 0, 6 * 128 + 124, False, "bf16"),     # group size 5 (the extra-head kernel)
     (2, 0, 64, 8, 64, 0, 12 * 128 + 124, False, "bf16"),    # group size 8 (two head groups)
     (2, 0, 128, 8, 48, 0, 12 * 128 + 124, False, "bf16"),   # group size 16 (two head chunks read the new row)
     (4, 1, 32, 8, 64, 0, 12 * 128 + 124, True, "bf16"),     # 4 bits, compact aux, paged body
     (2, 1, 32, 8, 32, 128, 126, False, "bf16"),             # sink tokens, then the first residual rows
-    (2, 0, 32, 8, 96, 0, 6 * 128 + 124, False, "fp32"),     # fp32 tokens: the two kernels every step
+    (2, 0, 32, 8, 96, 0, 6 * 128 + 124, False, "fp32"),     # fp32 tokens, dense: fused but for the flush
+    (2, 0, 32, 8, 1, 0, 40 * 128 + 124, False, "fp32"),     # the same with eleven workgroups per stream and the merge
+    (2, 0, 32, 8, 6, 0, 6 * 128 + 124, True, "fp32"),       # fp32 tokens, paged: the two kernels every step
+    (4, 1, 40, 8, 3, 0, 2 * 128 + 124, True, "fp32"),       # the same with the extra-head kernel, compact aux
 ]
 
 
