@@ -683,7 +683,7 @@ __device__ void quantize_tile(const void* src, bool bf16, int64_t tstride, int k
             s[m] = step == 0.f ? 1.f : step;
             off[m] = mn[m];
         }
-        const float r = __builtin_amdgcn_rcpf(s[m]);  // one Newton step: rounded to within an ulp
+        const float r = __builtin_amdgcn_rcpf(s[m]);  // one Newton step: the division's result, over every mantissa
         inv_s[m] = fmaf(fmaf(-s[m], r, 1.f), r, r);
     }
     // (steps near the ends of the fp32 range, where the reciprocal or the step is subnormal)
