@@ -152,9 +152,9 @@ def test_decode_validation(K):
     p = K.kvarn_params_init(2)
     c = _HostCache(K, batch=2, n_kv=2, max_blocks=32)
     keep, buf = _fake(1 << 20)
-    need = K.kvarn_decode_workspace_bytes(p, c, 8, 4096)  # 4 streams x 32 tiles: split
+    need = K.kvarn_decode_workspace_bytes(p, c, 8, 4096)  # 4 streams x 32 tiles: room for partials
     assert need > 0
-    assert K.kvarn_decode_workspace_bytes(p, c, 8, 384) == 0  # 3 tiles: one split, no partials
+    assert K.kvarn_decode_workspace_bytes(p, c, 8, 384) == 0  # 3 tiles: one workgroup, no partials
     good = dict(n_q=8, q=buf, q_dtype=1, out=buf, out_dtype=1, sm_scale=0.088, max_len_hint=4096, workspace=buf,
                 workspace_bytes=need)
 
@@ -169,7 +169,7 @@ def test_decode_validation(K):
         with pytest.raises(K.KVarNError) as e:
             call(**kw)
         assert e.value.status == code, kw
-    # the workspace grows with the split plan and the number of query heads
+    # the workspace grows with the number of query heads
     assert K.kvarn_decode_workspace_bytes(p, c, 16, 4096) == 2 * need
     assert K.kvarn_decode_workspace_bytes(p, c, 8, -1) == 0
 
@@ -197,7 +197,7 @@ def test_append_decode_validation(K):
 
 def test_decode_noalloc_validation(K):
     """The allocation-free decode validates like kvarn_decode_attention, before any HIP call, and
-    every split plan's partials fit its scratch array."""
+    every size that kvarn_decode_workspace_bytes gives fits its scratch array."""
     p = K.kvarn_params_init(2)
     c = _HostCache(K, batch=2, n_kv=2, max_blocks=32)
     keep, buf = _fake(1 << 20)
@@ -207,10 +207,8 @@ def test_decode_noalloc_validation(K):
         with pytest.raises(K.KVarNError) as e:
             K.kvarn_decode_attention_noalloc(p, c, **{**good, **kw}, stream=0)
         assert e.value.status == code, kw
-    # The largest plan with partials in memory: 255 streams of 8 query heads in 9 splits, 18.2 MiB
-    # (from 256 streams on, 4 splits per stream give every SIMD a wave and the plan stops there).
-    # Plans of up to 4 splits whose LDS blocks fit merge inside the workgroup and need none (511
-    # streams of 8 heads in 4 splits, 1023 in 3, 1023 streams of 16 heads in 2).
+    # The largest size: 255 streams of 8 query heads, 9 partials each, 18.2 MiB.  From 256 streams on every
+    # stream is merged inside its workgroup, without a workspace.
     mid = _HostCache(K, batch=255, n_kv=1, max_blocks=2049)
     need = K.kvarn_decode_workspace_bytes(p, mid, 8, 2048 * 128)
     assert need == 255 * 8 * 9 * 1040 <= K.NOALLOC_SCRATCH_BYTES

@@ -76,7 +76,7 @@ def _decode(K, built, q):
 
 @pytest.mark.parametrize("bits,n_sink,name", [(2, 0, "llama"), (4, 128, "llama"), (2, 0, "stress")])
 def test_compact_decode(K, bits, n_sink, name):
-    """Decode over compact tiles: group sizes 4 and 5, sink, ragged lengths, split plan."""
+    """Decode over compact tiles: group sizes 4 and 5, sink, ragged lengths."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build(name, bits=bits, n_sink=n_sink, context=n_sink + 20 * 128 + 77, batch=3, aux=1)
     assert K.kvarn_tile_bytes(built.params) == (4608 if bits == 2 else 8704)

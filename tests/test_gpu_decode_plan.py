@@ -25,6 +25,13 @@ pytestmark = pytest.mark.gpu
     (100, 12, 3, 2, 0, 0, 65),   # 300 long streams, the longest sequences first (a batch above a wave)
     (33, 80, 8, 2, 0, 20, 34),   # 528 streams (two head chunks): 4 waves, the longest first
     (400, 8, 2, 2, 0, 7, 3),     # 800 streams: 2 waves
+    (400, 8, 2, 2, 0, 0, 33),    # 800 longer streams: 4 waves, too many sequences to rank
+    (100, 32, 8, 2, 1, 0, 33),   # 800 of fewer sequences, the longest first
+    (300, 8, 2, 2, 0, 0, 65),    # 600 long streams of more sequences than a wave ranks
+    (22, 64, 8, 2, 0, 0, 72),    # 176 streams that may be ragged: 4 workgroups
+    (576, 8, 2, 4, 0, 0, 16),    # 1152 streams at 4 bits: 4 waves
+    (800, 8, 2, 2, 0, 3, 16),    # 1600 streams: 4 waves
+    (1600, 4, 2, 2, 1, 0, 2),    # 3200 streams: 1 wave
 ])
 def test_decode_plan_edges(batch, n_q, n_kv, bits, aux, n_sink, tiles):
     from paper_2606_03458_amd import kvarn as K

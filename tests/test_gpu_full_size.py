@@ -131,7 +131,7 @@ def _end_to_end(p, cache, e2e, out, q, g, prompt, n_append, aux, out_dtype):
 
 def test_full_size_throughput(K):
     """32 layers x batch 32 (1024 sequences), 32 q / 8 kv heads, 32768-token 2-bit cache plus
-    132 appended tokens (one flush), bf16 q and output, a single split per stream."""
+    132 appended tokens (one flush), bf16 q and output, a single wave per stream."""
     _run(K, "throughput", n_append=132, n_streams=64, n_tiles=12, out_dtype=torch.bfloat16)
 
 

@@ -107,16 +107,21 @@ def test_quantize_deterministic(K):
 
 # ---- decode attention ---------------------------------------------------------------------
 
+UNWRITTEN = 7.25e30  # (no logit's maximum)
+
+
 def _decode(K, built, q, out_dtype=torch.float32, max_len=None):
     p, cache = built.params, built.cache
     max_len = built.length + 1 if max_len is None else max_len
     ws_bytes = K.kvarn_decode_workspace_bytes(p, cache, built.n_q, max_len)
-    ws = torch.zeros(ws_bytes, dtype=torch.uint8, device="cuda")
+    ws = torch.full((ws_bytes // 4,), UNWRITTEN, device="cuda")
     out = torch.empty(q.shape, dtype=out_dtype, device="cuda")
     qd = K.KVARN_F32 if q.dtype == torch.float32 else K.KVARN_BF16
     od = K.KVARN_F32 if out_dtype == torch.float32 else K.KVARN_BF16
     K.kvarn_decode_attention(p, cache, built.n_q, q, qd, out, od, SCALE, max_len, ws, ws_bytes)
     torch.cuda.synchronize()
+    # partials (260 floats, the maximum first) that the call wrote per query head: workgroups per stream
+    built.partials = int((ws[::260] != UNWRITTEN).sum()) / (cache.batch * built.n_q)
     return out
 
 
@@ -165,7 +170,7 @@ def test_decode_llama_layer(K, out_dtype):
                                               (4, 128, "stress"), (2, 100, "llama"), (4, 100, "stress")])
 def test_decode_variants(K, bits, n_sink, name):
     """Sink region, 4-bit codes, GQA 5, ragged lengths (including 0 and sink-only) and a
-    residual, on a small batch that the split-K plan divides into many splits."""
+    residual, on a small batch whose streams take several workgroups each."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build(name, bits=bits, n_sink=n_sink, context=n_sink + 20 * 128 + 77, batch=5)
     lens = [built.length, n_sink + 2 * 128, n_sink + 131, n_sink // 2 if n_sink else 0, 0]
@@ -175,17 +180,17 @@ def test_decode_variants(K, bits, n_sink, name):
     check_output(out.cpu().numpy(), _ref(built, q), bf16_out=False)
 
 
-@pytest.mark.parametrize("batch,n_sink,body,n_split", [
-    (2, 100, 20, 18),   # 10 body splits + one per sink / residual chunk (4 + 4)
-    (31, 0, 20, 11),    # 10 body splits + one split for all chunks (one per chunk would not fit)
-    (31, 0, 24, 12),    # 12 body splits sharing the chunks
+@pytest.mark.parametrize("batch,n_sink,body,parts,partials", [
+    (2, 100, 20, 18, 7),   # 28 units (tiles, 32-token chunks): seven workgroups of four waves, one unit each
+    (31, 0, 20, 11, 0),    # 24 units, a whole CU's twelve waves: two each, chunks and tiles mixed
+    (31, 0, 24, 12, 0),    # 28 units: some waves three
 ])
-def test_decode_residual_placement(K, batch, n_sink, body, n_split):
-    """The three places the split plan gives a stream's sink and residual chunks (32 tokens
-    each) when the partials go to memory (fewer than 256 streams): a split per chunk, one split
-    for all chunks, or the body splits in turn.  Ragged lengths
-    give every residual size class (empty, one token, a partial and full chunks, 127 tokens) and a
-    sink-only sequence; the split count is checked through the workspace size."""
+def test_decode_residual_placement(K, batch, n_sink, body, parts, partials):
+    """Where a stream's sink and residual chunks (32 tokens each) may fall among its waves: a wave of
+    their own, or after the last tiles of a wave, in several workgroups or one.  Ragged lengths give
+    every residual size class (empty, one token, a partial and full chunks, 127 tokens) and a
+    sink-only sequence.  parts: partials per head that the workspace has room for (callers keep buffers
+    of that size); partials: those that the call writes."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", n_sink=n_sink, context=n_sink + body * 128 + 77, batch=batch)
     L = built.length
@@ -194,21 +199,21 @@ def test_decode_residual_placement(K, batch, n_sink, body, n_split):
     lens = [cycle[i % len(cycle)] for i in range(batch)]
     built.cache.seq_len.copy_(torch.tensor(lens, dtype=torch.int32))
     ws_bytes = K.kvarn_decode_workspace_bytes(built.params, built.cache, built.n_q, L + 1)
-    assert ws_bytes == batch * built.n_q * n_split * 1040
+    assert ws_bytes == batch * built.n_q * parts * 1040
     q = workloads.decode_queries(built, seed=9)
     out = _decode(K, built, q)
+    assert built.partials == partials
     check_output(out.cpu().numpy(), _ref(built, q), bf16_out=False)
 
 
-@pytest.mark.parametrize("bits,n_q,body,n_split", [
-    (2, 16, 64, 68),   # 32 body splits + one split per sink / residual chunk (32 + 4)
-    (2, 16, 3, 1),     # one wave per stream walks all 36 chunks after its 3 tiles
-    (4, 40, 20, 46),   # 4 bits, group size 10 (two chunks of 5 heads: the extra-head kernel)
+@pytest.mark.parametrize("bits,n_q,body,parts,partials", [
+    (2, 16, 64, 68, 25),   # 100 units: 25 workgroups of four waves
+    (2, 16, 3, 0, 0),      # 39 units without room for partials: one workgroup of twelve waves
+    (4, 40, 20, 46, 14),   # 4 bits, group size 10 (two chunks of 5 heads: the extra-head kernel)
 ])
-def test_decode_max_sink(K, bits, n_q, body, n_split):
+def test_decode_max_sink(K, bits, n_q, body, parts, partials):
     """The largest sink the library takes (1024 bf16 tokens: 32 chunks per stream) with a
-    residual, ragged lengths down to sink-only and empty; the split count through the workspace
-    size."""
+    residual, ragged lengths down to sink-only and empty (parts, partials: as above)."""
     from paper_2606_03458_amd import workloads
     ns = 1024
     built, _ = workloads.build("llama", bits=bits, n_q=n_q, n_kv=4, batch=4, n_sink=ns, context=ns + body * 128 + 77)
@@ -216,16 +221,17 @@ def test_decode_max_sink(K, bits, n_q, body, n_split):
     lens = [L, ns + 5, ns - 1, 0]
     built.cache.seq_len.copy_(torch.tensor(lens, dtype=torch.int32))
     ws_bytes = K.kvarn_decode_workspace_bytes(built.params, built.cache, built.n_q, L + 1)
-    assert ws_bytes == (4 * n_q * n_split * 1040 if n_split > 1 else 0)
+    assert ws_bytes == 4 * n_q * parts * 1040
     q = workloads.decode_queries(built, seed=12)
     out = _decode(K, built, q)
+    assert built.partials == partials
     check_output(out.cpu().numpy(), _ref(built, q), bf16_out=False)
 
 
 def test_decode_long_context(K):
-    """One sequence of 262,221 tokens (2048 body tiles per kv head, 8 kv heads): 342 body splits
-    of 6 tiles and 4 residual-chunk splits per stream, merged by four waves per query head over
-    346 partials."""
+    """One sequence of 262,221 tokens (2048 body tiles per kv head, 8 kv heads): 32 workgroups of four
+    waves per stream, 16 or 17 units each wave, merged by four waves per query head (the workspace has
+    room for 346 partials)."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", batch=1, context=2048 * 128 + 77)
     L = built.length
@@ -233,20 +239,19 @@ def test_decode_long_context(K):
     assert ws_bytes == 1 * 32 * 346 * 1040
     q = workloads.decode_queries(built, seed=13)
     out = _decode(K, built, q)
+    assert built.partials == 32
     check_output(out.cpu().numpy(), _ref(built, q), bf16_out=False)
 
 
 @pytest.mark.parametrize("bits,n_q,batch,aux,n_sink", [
-    (2, 8, 768, 0, 0),     # group 4: 1536 streams, two splits each
-    (4, 8, 512, 1, 128),   # group 4 at 4 bits, compact aux, a sink for the second split
-    (2, 10, 512, 0, 0),    # group 5 (the extra-head variant)
-    (4, 16, 512, 0, 100),  # group 8 (two head groups) at 4 bits, partial sink chunks
+    (2, 8, 768, 0, 0),     # 1536 streams, group size 4: two waves
+    (4, 8, 512, 1, 128),   # 1024 at 4 bits, compact aux, a sink: two waves
+    (2, 10, 512, 0, 0),    # group size 5 (the extra-head variant): two waves
+    (4, 16, 512, 0, 100),  # group size 8 (two head groups) at 4 bits, partial sink chunks: two waves
 ])
 def test_decode_pair_mode(K, bits, n_q, batch, aux, n_sink):
-    """Streams of exactly two splits that share the sink/residual chunks (batch x 2 kv heads just
-    below two rounds of resident waves) run as the two waves of one workgroup and merge there: no
-    workspace.  Ragged lengths give a second split without body tiles, a sink-only and an empty
-    sequence."""
+    """Streams of two waves, which share a workgroup and merge there: no workspace.  Ragged lengths give
+    a second wave without body tiles, a sink-only and an empty sequence."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", bits=bits, n_q=n_q, n_kv=2, batch=batch, aux=aux, n_sink=n_sink,
                                context=n_sink + 4 * 128 + 77)
@@ -254,7 +259,6 @@ def test_decode_pair_mode(K, bits, n_q, batch, aux, n_sink):
     cycle = [L, n_sink + 2 * 128 + 5, n_sink + 128, n_sink + 3, n_sink // 2, 0, L - 64]
     lens = [cycle[i % len(cycle)] for i in range(batch)]
     built.cache.seq_len.copy_(torch.tensor(lens, dtype=torch.int32))
-    # (one split per stream would leave a third of the wave slots empty: the plan is two splits)
     assert K.kvarn_decode_workspace_bytes(built.params, built.cache, n_q, L + 1) == 0
     q = workloads.decode_queries(built, seed=10)
     out = _decode(K, built, q)
@@ -262,19 +266,19 @@ def test_decode_pair_mode(K, bits, n_q, batch, aux, n_sink):
 
 
 @pytest.mark.parametrize("bits,n_q,batch,tiles,aux,n_sink", [
-    (2, 32, 80, 8, 0, 0),     # group 4: 3 body splits + one sink/residual split (a short stream)
-    (2, 32, 64, 50, 0, 0),    # group 4: 4 body splits sharing the residual chunks
-    (2, 32, 96, 6, 1, 0),     # group 4, compact aux: 3 body splits + one sink/residual split
-    (4, 32, 64, 12, 0, 128),  # group 4 at 4 bits with a sink: 3 body splits + one sink/residual split
-    (4, 32, 64, 50, 1, 100),  # the same at 4 bits, compact aux, 4 body splits sharing the chunks
-    (2, 40, 48, 6, 0, 0),     # group 5 (the extra-head variant): 3 body splits + one residual split
-    (2, 64, 64, 12, 0, 0),    # group 8 (two head groups): 3 body splits + one residual split
-    (2, 128, 48, 12, 0, 0),   # group 16 (two chunks of 8 heads, a workgroup per chunk): 3 body splits
+    (2, 32, 80, 8, 0, 0),     # 640 streams, group size 4, a short body
+    (2, 32, 64, 50, 0, 0),    # 512, a longer body, the longest sequences first
+    (2, 32, 96, 6, 1, 0),     # 768, compact aux: 10 units for four waves
+    (4, 32, 64, 12, 0, 128),  # 512 at 4 bits with a sink
+    (4, 32, 64, 50, 1, 100),  # the same at 4 bits, compact aux, a longer body
+    (2, 40, 48, 6, 0, 0),     # group size 5 (the extra-head variant)
+    (2, 64, 64, 12, 0, 0),    # group size 8 (two head groups)
+    (2, 128, 48, 12, 0, 0),   # group size 16 (two chunks of 8 heads, a workgroup per chunk)
 ])
 def test_decode_group_mode(K, bits, n_q, batch, tiles, aux, n_sink):
-    """Streams of three or four splits (batch x 8 kv heads, 384 to 768 streams) run as the waves
-    of one workgroup and merge there: no workspace.  Ragged lengths leave later splits without body
-    tiles, and give sink-only and empty sequences."""
+    """Streams of four waves (batch x 8 kv heads, 384 to 768 streams), one workgroup each, which merge
+    there: no workspace.  Ragged lengths leave later waves without body tiles, and give sink-only and
+    empty sequences."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", bits=bits, n_q=n_q, n_kv=8, batch=batch, aux=aux, n_sink=n_sink,
                                context=n_sink + tiles * 128 + 77)
@@ -304,7 +308,7 @@ def test_decode_group_mode(K, bits, n_q, batch, tiles, aux, n_sink):
 @pytest.mark.parametrize("n_q,n_kv", [(2, 2), (4, 2), (6, 2), (8, 2), (10, 2), (12, 2), (32, 2)])
 def test_decode_group_sizes(K, n_q, n_kv):
     """Every query-group size class (1 .. 4, 5, 6 .. 8, 9 .. 16 take different kernels), with a
-    residual and enough body tiles for the plan to split every stream."""
+    residual and enough body tiles for every wave of a CU."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", context=12 * 128 + 45, batch=2, n_q=n_q, n_kv=n_kv)
     q = workloads.decode_queries(built, seed=6)
@@ -333,7 +337,7 @@ def test_decode_peaked_softmax(K, mult):
 
 
 def test_decode_length_above_hint(K):
-    """A max_len_hint below the true length still attends every token (last split extends)."""
+    """A max_len_hint below the true length still attends every token (the waves share the true length)."""
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", context=2048, batch=1)
     q = workloads.decode_queries(built, seed=4)
@@ -342,8 +346,8 @@ def test_decode_length_above_hint(K):
 
 
 def test_decode_workspace_reuse(K):
-    """One workspace serves consecutive calls on caches of different shapes and split plans (more
-    streams after fewer, many splits after few; every kernel family): each call rewrites what it
+    """One workspace serves consecutive calls on caches of different shapes and plans (more streams
+    after fewer, many workgroups per stream after few; every kernel family): each call rewrites what it
     reads, so every output equals that of a call with a fresh workspace."""
     from paper_2606_03458_amd import workloads
     cases = []

@@ -1,7 +1,7 @@
 """The allocation-free decode entry point (kvarn_decode_attention_noalloc) through the C ABI:
 its output equals kvarn_decode_attention's on the same cache and queries (the same kernels,
-the split partials in the library's per-device scratch array instead of a caller workspace),
-and meets the output bar against the oracle, on consecutive calls whose split plans shrink, so
+the workgroups' partials in the library's per-device scratch array instead of a caller workspace),
+and meets the output bar against the oracle, on consecutive calls whose plans shrink, so
 that a later call finds the earlier call's partials in the shared array."""
 import numpy as np
 import pytest
@@ -27,7 +27,7 @@ def _case(K, batch, n_q, n_kv, context, bits, aux, n_sink, seed):
     from paper_2606_03458_amd import workloads
     built, _ = workloads.build("llama", bits=bits, n_sink=n_sink, context=context, batch=batch, n_q=n_q, n_kv=n_kv,
                                aux=aux)
-    lens = [context - 131 * b for b in range(batch)]  # ragged: the plan still splits the longest
+    lens = [context - 131 * b for b in range(batch)]  # ragged
     built.cache.seq_len.copy_(torch.tensor(lens, dtype=torch.int32))
     q = workloads.decode_queries(built, seed=seed)
     return built, q
@@ -51,7 +51,7 @@ def test_noalloc_equals_decode(K):
         (3, 40, 8, 40 * 128 + 77, 2, 0, 0),
         (2, 32, 8, 24 * 128 + 5, 4, 1, 128),
         (1, 8, 2, 12 * 128 + 100, 2, 0, 0),
-        (2, 8, 2, 3 * 128 + 3, 2, 0, 0),  # one split per stream: no partials at all
+        (2, 8, 2, 3 * 128 + 3, 2, 0, 0),  # one workgroup per stream: no partials at all
     ]
     sizes = []
     for i, (B, nq, nkv, T, bits, aux, ns) in enumerate(cases):
