@@ -212,9 +212,11 @@ KVARN_API int kvarn_prefill(const kvarn_params *p, const kvarn_cache *cache, con
 KVARN_API int kvarn_append_token(const kvarn_params *p, const kvarn_cache *cache, const void *k_new, const void *v_new,
                        int32_t dtype, int32_t host_len_before, hipStream_t stream);
 
-/* Workspace bytes that kvarn_decode_attention needs for these sizes (split partials); 0 when
- * the plan keeps every (sequence, kv head) in one split or in a few splits merged inside one
- * workgroup, or when an argument is invalid. */
+/* Workspace bytes that kvarn_decode_attention asks for with these sizes: room for the partials of
+ * (sequence, kv head) pairs that take several workgroups; 0 for 256 pairs (for more than 8 query heads
+ * per kv head, each counted ceil(heads / 8) times) and more, for short sequences, and when an argument
+ * is invalid.  A call may write fewer partials than there is room for, or none, but a buffer of this
+ * size has to be there. */
 KVARN_API size_t kvarn_decode_workspace_bytes(const kvarn_params *p, const kvarn_cache *cache, int32_t n_q,
                                     int32_t max_len_hint);
 
@@ -226,7 +228,7 @@ KVARN_API size_t kvarn_decode_workspace_bytes(const kvarn_params *p, const kvarn
  *   rotated domain, and the body's output is rotated back once per query head (App. A).
  *   q    [batch][n_q][128] fp32 or bf16 (post-RoPE, unrotated)
  *   out  [batch][n_q][128] in out_dtype (fp32 or bf16)
- *   max_len_hint  an upper bound of every seq_len (sizes the split-K plan)
+ *   max_len_hint  an upper bound of every seq_len (sizes the launch plan)
  *   workspace  device buffer of at least kvarn_decode_workspace_bytes(...) bytes, 16-byte
  *           aligned; may be NULL when that size is 0
  * n_q must be a positive multiple of n_kv with n_q / n_kv <= 16; q 4-byte and out 8-byte
@@ -263,7 +265,7 @@ KVARN_API int kvarn_append_decode(const kvarn_params *p, const kvarn_cache *cach
 /*
  * Decode attention that allocates nothing, for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid allocation.
- * Arguments and results are those of kvarn_decode_attention without the workspace: the split
+ * Arguments and results are those of kvarn_decode_attention without the workspace: the workgroups'
  * partials go to a scratch array of KVARN_NOALLOC_SCRATCH_BYTES (32 MiB) that the library
  * holds in static device memory, one array per device, kept until the process ends.  Its
  * device address is looked up once per device (hipGetSymbolAddress, on the first call with

@@ -1,4 +1,4 @@
-// Host side of the libkvarn C ABI: argument validation (before anything is enqueued), split
+// Host side of the libkvarn C ABI: argument validation (before anything is enqueued), launch
 // planning and kernel launches.  No device memory is allocated here.
 #include <cmath>
 #include <cstdint>

@@ -1172,18 +1172,18 @@ void k_decode4(DecodeArgs a) {
     }
 }
 
-// Merge of the split partials of a (sequence, query head): log-sum-exp weights, the inverse
+// Merge of the workgroups' partials of a (sequence, query head): log-sum-exp weights, the inverse
 // rotation of the body part in registers (lane l holds channels 2l, 2l + 1), normalisation.
 // W waves per (sequence, query head), 256 threads per workgroup: W = 1 (four heads per
-// workgroup) for few splits; W = 4 for many, wave w summing splits w, w + 4, ... and wave 0
-// adding the four sums in a fixed order (eight waves per head measured slower at 37 splits).
-constexpr int kMergeWide = 9;  // from this many splits on, four waves per head
+// workgroup) for few partials; W = 4 for many (a plan makes at most 32), wave w summing partials w,
+// w + 4, ... and wave 0 adding the four sums in a fixed order.
+constexpr int kMergeWide = 9;  // from this many partials on, four waves per head
 
 template <int W>
 __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
     static_assert(W == 1 || W == 4, "one or four waves per head");
     constexpr int HPB = 4 / W;          // heads per workgroup
-    constexpr int U = W == 1 ? 8 : 16;  // splits with loads in flight per wave
+    constexpr int U = W == 1 ? 8 : 16;  // partials with loads in flight per wave
     __shared__ float red[W > 1 ? W - 1 : 1][2 * kD + 2];
     const int l = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1194,9 +1194,9 @@ __global__ __launch_bounds__(256) void k_decode_merge(DecodeArgs a) {
     if (bh >= (size_t)a.n_rows) return;
     const float* P = a.ws + bh * a.n_wg * kPart;
     const int S = a.n_wg;
-    // Log-sum-exp over this wave's splits, U of them with every load in flight (indices past the
-    // last split are clamped, their values unused), the sums kept relative to the running
-    // maximum M of the splits that hold a probability mass.
+    // Log-sum-exp over this wave's partials, U of them with every load in flight (indices past the
+    // last one are clamped, their values unused), the sums kept relative to the running
+    // maximum M of the partials that hold a probability mass.
     float M = -INFINITY, L = 0.f, acc[2] = {0.f, 0.f}, pl[2] = {0.f, 0.f};
     for (int s0 = part; s0 < S; s0 += U * W) {
         float mm[U], ll[U];

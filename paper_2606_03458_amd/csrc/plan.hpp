@@ -22,8 +22,8 @@ struct DecodePlan {
 
 // Partials per query head that kvarn_decode_workspace_bytes leaves room for: one for each share
 // of at least two body tiles and one per sink or residual chunk, of the streams (sequence, kv
-// head, head chunk) that are too few to fill the card; 0 where no plan writes partials.  Callers
-// keep buffers of this size, so it is part of the interface; a plan takes fewer.
+// head, head chunk) that are too few to fill the card.  Callers keep buffers of this size, so it is
+// part of the interface; a plan takes fewer, at most 32, or none.  Where this is 0 it takes none.
 inline int workspace_parts(long long streams, int nb, int max_len, int n_sink, int per_simd) {
     const long long slots = 1024LL * per_simd;
     if (streams * 4 >= 1024) return 0;
