@@ -432,7 +432,7 @@ def streaming(args):
 
 
 PROFILES = os.path.join(ROOT, "profiles")
-DECODE_SOURCES = [os.path.join(ROOT, "paper_2606_03458_amd", "csrc", f) for f in ("decode.hip", "common.hpp")]
+DECODE_SOURCES = [os.path.join(ROOT, "paper_2606_03458_amd", "csrc", f) for f in ("decode.hip", "common.hpp", "plan.hpp")]
 QUANT_SOURCES = [os.path.join(ROOT, "paper_2606_03458_amd", "csrc", f) for f in ("quantize.hip", "common.hpp")]
 
 

@@ -57,7 +57,9 @@ inline DecodePlan plan_decode(int batch, int n_kv, int n_q, int bits, int max_le
     p.n_wg = 1;
     // More workgroups than CUs: the longest sequences go first, so that no long one starts when the
     // others are done (ragged 384 streams at 16k tokens: 58 -> 50).  Ranking a ragged batch costs a wave
-    // up to 3 us, so only where a sequence may hold 32 tiles or more.
+    // up to 3 us, so only where a sequence may hold 32 tiles or more.  A wave ranks two sequences per lane;
+    // larger batches go as they come, and lose what ranking gains (832 ragged streams at 8k: 49 -> 46 and
+    // 54 -> 47 of two draws).
     p.order = !equal && streams > 256 && batch > 1 && batch <= kOrderBatch && nb >= 32;
     const long long round = 1024LL * per_simd;  // waves that the card holds
     if (streams >= round) {

@@ -877,7 +877,7 @@ struct TileArgs {
     int32_t* best_iter;
 };
 
-// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the compact and exact variants keep 5 to 9 values in
+// Grids of many tiles: 4 waves per SIMD (128 VGPRs; the compact and exact variants keep 5 to 7 values in
 // scratch, the others none, one in the flush) hide the barrier and LDS latency of the reductions better
 // than 3 (measured 11 % faster).  So does the flush, whose grids are one tile per stream and
 // K/V: 1024 tiles fit the card at once (56 us against 67 at 3).
