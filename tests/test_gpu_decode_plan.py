@@ -21,7 +21,9 @@ pytestmark = pytest.mark.gpu
     (1, 32, 8, 2, 1, 128, 65),   # 19 workgroups
     (16, 64, 8, 4, 0, 0, 61),    # 4 workgroups, merged by one wave per head
     (129, 8, 2, 2, 0, 0, 5),     # 258 streams: 4 waves
-    (129, 8, 2, 2, 1, 0, 96),    # 258 long streams: 12 waves
+    (129, 8, 2, 2, 1, 0, 96),    # 258 long streams: 4 waves
+    (180, 8, 2, 2, 1, 0, 70),    # 360 long streams: 12 waves
+    (140, 16, 2, 2, 0, 0, 97),   # 280 long streams of two head groups: 8 waves
     (100, 12, 3, 2, 0, 0, 65),   # 300 long streams, the longest sequences first (a batch above a wave)
     (33, 80, 8, 2, 0, 20, 34),   # 528 streams (two head chunks): 4 waves, the longest first
     (400, 8, 2, 2, 0, 7, 3),     # 800 streams: 2 waves
